@@ -429,29 +429,29 @@ def cdag_autotune(h, prec: str = "fp64", batched: bool = True, reps: int = 3,
     return n.value
 
 
-def fetch_correlators(h, nts: Sequence[int]) -> List[np.ndarray]:
-    """Per input graph, complex128 [nt(g)]; nts: Nt of each graph in input order."""
-    total = 2 * int(sum(nts))
-    buf = np.empty(max(1, total), dtype=np.float64)
-    _check(lib().fetch_correlators(h, buf.ctypes.data_as(C.POINTER(C.c_double)), total))
+def _rows(fetch, h, nts: Sequence[int]) -> List[np.ndarray]:
+    """One call of `fetch` into one buffer of sum(nts) complex values, cut into a
+    view per entry of nts.  (Built entry by entry from its re and im parts, the
+    list took 1.2 us a row: 2.4 ms for the 2,000 rows of a meson DAG whose
+    execute takes 5.8 ms.)"""
+    buf = np.empty(int(sum(nts)), dtype=np.complex128)
+    _check(fetch(h, buf.ctypes.data_as(C.POINTER(C.c_double)), 2 * buf.size))
+    if len(nts) and len(set(nts)) == 1:
+        return list(buf.reshape(len(nts), nts[0]))
     out, o = [], 0
     for nt in nts:
-        v = buf[o:o + 2 * nt]
-        out.append(v[0::2] + 1j * v[1::2])
-        o += 2 * nt
+        out.append(buf[o:o + nt])
+        o += nt
     return out
+
+
+def fetch_correlators(h, nts: Sequence[int]) -> List[np.ndarray]:
+    """Per input graph, complex128 [nt(g)]; nts: Nt of each graph in input order."""
+    return _rows(lib().fetch_correlators, h, nts)
 
 
 def cdag_fetch_sums(h, nts: Sequence[int]) -> List[np.ndarray]:
-    total = 2 * int(sum(nts))
-    buf = np.empty(max(1, total), dtype=np.float64)
-    _check(lib().cdag_fetch_sums(h, buf.ctypes.data_as(C.POINTER(C.c_double)), total))
-    out, o = [], 0
-    for nt in nts:
-        v = buf[o:o + 2 * nt]
-        out.append(v[0::2] + 1j * v[1::2])
-        o += 2 * nt
-    return out
+    return _rows(lib().cdag_fetch_sums, h, nts)
 
 
 # ------------------------------------------------------------------ object wrapper

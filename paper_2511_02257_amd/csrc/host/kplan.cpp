@@ -342,6 +342,7 @@ KernelPlan make_kernel_plan(const Dag& d, const Plan& p, int prec, const TileTab
   for (size_t g = 0; g < d.corr.size(); ++g) by_corr[d.corr[g]].push_back((int64_t)g);
   std::vector<XsumDesc> xd;
   std::vector<XsumEntry> xe;
+  int64_t xitems = 0;
   for (int32_t c = 0; c < n_corr; ++c) {
     XsumDesc x{};
     x.out_off = kp.sum_corr_off[c];   // relative; fixed up below
@@ -350,10 +351,12 @@ KernelPlan make_kernel_plan(const Dag& d, const Plan& p, int prec, const TileTab
       xe.push_back({kp.tree_corr_off[tree_of[d.root_of_graph[g]]], d.w_re[g], d.w_im[g]});
     x.e_end = (int32_t)xe.size();
     x.nt = kp.sum_nt[c];
+    x.item_begin = (int32_t)xitems;   // a correlator without graphs (nt 0) has no items
+    xitems += x.nt;
     xd.push_back(x);
   }
   while (kp.blob.size() % 16) kp.blob.push_back(0);
-  kp.xsum = {L_XSUM, 0, (int32_t)xd.size(), 0, (int64_t)xd.size(), (int64_t)kp.blob.size()};
+  kp.xsum = {L_XSUM, 0, (int32_t)xd.size(), 0, xitems, (int64_t)kp.blob.size()};
   for (auto& x : xd) put(kp.blob, x);
   const int64_t entries_host = (int64_t)kp.blob.size();
   for (auto& e : xe) put(kp.blob, e);

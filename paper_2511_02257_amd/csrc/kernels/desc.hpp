@@ -86,7 +86,7 @@ struct HcaDesc {
 // (ascending input graph) of w * C_root(t), in a fixed order.
 struct XsumDesc {
   int64_t out_off;                             // [nt][2] doubles
-  int32_t e_begin, e_end, nt, pad;
+  int32_t e_begin, e_end, nt, item_begin;      // items: one per time slice
 };
 struct XsumEntry {
   int64_t root_off;                            // [nt][2] doubles

@@ -55,41 +55,76 @@ __global__ void __launch_bounds__(256, 3) hca_trace(char* __restrict__ arena, co
 }
 
 // ------------------------------------------------------------------ cross-diagram sum (FP64)
-// One workgroup per correlator.  Thread i sums the entries i, i + 256, ... in
-// that order; the 256 partial sums are then added in a fixed tree.  The order
-// is fixed, so the result does not change from run to run.
+// The last kernel of an execute: one workgroup per (correlator, t), then
+// workgroups that copy the correlators to the host.  Thread i sums the entries
+// i, i + 256, ... in that order; the 256 partial sums are then added in a fixed
+// tree (halves 128, 64, then 32 .. 1 within a wave).  The order is fixed, so
+// the result does not change from run to run.
+//
+// host (may be nullptr): pinned memory laid out as [corr_bytes of
+// correlators][sums] like the arena from corr_off; the kernel stores both
+// there, so no copy follows it.
+//
+// Bound by the latency of an entry's two dependent loads (once per 256
+// entries), or by the host link for many correlators.  With one workgroup per
+// correlator walking over t it took 9.8 us (8 time slices, 6 graphs) and 53 us
+// (32 slices, 2,000 graphs), and the copy that followed it 9 and 29 us with the
+// gap before it; this form, the copy included, takes 2.3 and 22 us (1 MB at
+// 45 GB/s).
 __global__ void __launch_bounds__(256) xsum_kernel(char* __restrict__ arena, const XsumDesc* __restrict__ descs,
-                                                   const XsumEntry* __restrict__ entries, int n_desc) {
-  __shared__ double red[2][256];
+                                                   const XsumEntry* __restrict__ entries, int n_desc, int64_t n_items,
+                                                   int64_t corr_off, int64_t corr_bytes, char* __restrict__ host) {
+  typedef double v2d __attribute__((ext_vector_type(2)));
+  __shared__ double red[2][128];
   const int tid = threadIdx.x;
-  for (int c = blockIdx.x; c < n_desc; c += gridDim.x) {
-    const XsumDesc& x = descs[c];
-    double* out = reinterpret_cast<double*>(arena + x.out_off);
-    for (int t = 0; t < x.nt; ++t) {
-      double sr = 0.0, si = 0.0;
-      for (int e = x.e_begin + tid; e < x.e_end; e += 256) {
-        const double* C = reinterpret_cast<const double*>(arena + entries[e].root_off);
-        const double cr = C[2 * t], ci = C[2 * t + 1];
-        sr += entries[e].w_re * cr - entries[e].w_im * ci;
-        si += entries[e].w_re * ci + entries[e].w_im * cr;
-      }
+  for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+    const XsumDesc& x = descs[find_desc(&descs[0].item_begin, sizeof(XsumDesc) / 4, n_desc, item)];
+    const int t = (int)(item - x.item_begin);
+    double sr = 0.0, si = 0.0;
+    for (int e = x.e_begin + tid; e < x.e_end; e += 256) {
+      const double* C = reinterpret_cast<const double*>(arena + entries[e].root_off);
+      const double cr = C[2 * t], ci = C[2 * t + 1];
+      sr += entries[e].w_re * cr - entries[e].w_im * ci;
+      si += entries[e].w_re * ci + entries[e].w_im * cr;
+    }
+    if (tid >= 128) {
+      red[0][tid - 128] = sr;
+      red[1][tid - 128] = si;
+    }
+    __syncthreads();
+    if (tid < 128) {
+      sr += red[0][tid];
+      si += red[1][tid];
+    }
+    __syncthreads();
+    if (tid >= 64 && tid < 128) {
       red[0][tid] = sr;
       red[1][tid] = si;
-      __syncthreads();
-      for (int w = 128; w > 0; w >>= 1) {
-        if (tid < w) {
-          red[0][tid] += red[0][tid + w];
-          red[1][tid] += red[1][tid + w];
-        }
-        __syncthreads();
+    }
+    __syncthreads();
+    if (tid < 64) {
+      sr += red[0][tid + 64];
+      si += red[1][tid + 64];
+#pragma unroll
+      for (int w = 32; w > 0; w >>= 1) {
+        sr += __shfl_down(sr, w);
+        si += __shfl_down(si, w);
       }
       if (tid == 0) {
-        out[2 * t] = red[0][0];
-        out[2 * t + 1] = red[1][0];
+        const int64_t off = x.out_off + 16LL * t;
+        *reinterpret_cast<v2d*>(arena + off) = v2d{sr, si};
+        if (host) *reinterpret_cast<v2d*>(host + (off - corr_off)) = v2d{sr, si};
       }
-      __syncthreads();
     }
+    __syncthreads();
   }
+  if (host == nullptr) return;
+  // the workgroups past the sums' (every one of a grid of less) copy the correlators
+  const int64_t first = n_items < (int64_t)gridDim.x ? n_items : 0;
+  const int64_t step = ((int64_t)gridDim.x - first) * 256, b = (int64_t)blockIdx.x - first;
+  if (b < 0) return;
+  const v2d* src = reinterpret_cast<const v2d*>(arena + corr_off);
+  for (int64_t i = b * 256 + tid; i < corr_bytes / 16; i += step) reinterpret_cast<v2d*>(host)[i] = src[i];
 }
 
 // ------------------------------------------------------------------ layout conversion
@@ -147,26 +182,26 @@ void set_args(KernelCall& k, char* arena, const void* desc, int n_desc, int64_t 
   k.desc = desc;
   k.n_desc = n_desc;
   k.n_items = n_items;
-  k.n_args = 4;
 }
 }  // namespace
 
 void KernelCall::bind() {
   args[0] = &arena;
   args[1] = &desc;
-  if (n_args == 5) {
+  if (entries != nullptr) {
     args[2] = &entries;
     args[3] = &n_desc;
-    args[4] = nullptr;
-  } else {
-    args[2] = &n_desc;
-    args[3] = &n_items;
-    if (n_args == 7) {
-      args[4] = &tdesc;
-      args[5] = &n_tdesc;
-      args[6] = &n_titems;
-    }
+    args[4] = &n_items;
+    args[5] = &corr_off;
+    args[6] = &corr_bytes;
+    args[7] = &host;
+    return;
   }
+  args[2] = &n_desc;
+  args[3] = &n_items;
+  args[4] = &tdesc;     // exterior contractions only
+  args[5] = &n_tdesc;
+  args[6] = &n_titems;
 }
 
 hipError_t launch(KernelCall& k, hipStream_t s) {
@@ -187,7 +222,6 @@ hipError_t hec_call(int prec, int variant, bool interior, char* arena, int64_t d
     k->block = kTileShapes[1].nth;
     k->grid = grid_for(n_items);
     set_args(*k, arena, arena + desc_off, n_desc, n_items);
-    k->n_args = 7;
     return hipSuccess;
   }
   if (variant < 0 || variant >= 4 * kNumTiles || prec < 0 || prec > 3) return hipErrorInvalidValue;
@@ -202,7 +236,6 @@ hipError_t hec_call(int prec, int variant, bool interior, char* arena, int64_t d
   k->fn = fn;
   k->block = kTileShapes[tile].nth;
   set_args(*k, arena, arena + desc_off, n_desc, n_items);
-  k->n_args = 7;
   if (traces) {
     // one workgroup per contraction work item, then the trace workgroups
     const int64_t blocks = n_items + trace_blocks(k->block, n_titems);
@@ -243,13 +276,18 @@ hipError_t hca_call(int prec, char* arena, int64_t desc_off, int n_desc, int64_t
   return hipSuccess;
 }
 
-hipError_t xsum_call(char* arena, int64_t desc_off, int64_t entries_off, int n_desc, KernelCall* k) {
+hipError_t xsum_call(char* arena, int64_t desc_off, int64_t entries_off, int n_desc, int64_t n_items,
+                     int64_t corr_off, int64_t corr_bytes, char* host, KernelCall* k) {
   k->fn = reinterpret_cast<const void*>(&xsum_kernel);
-  k->grid = grid_for(n_desc);
+  // 16 KB of correlators per copying workgroup, at most one per compute unit
+  const int64_t copiers = host ? std::min<int64_t>(256, (corr_bytes + 16383) / 16384) : 0;
+  k->grid = grid_for(n_items + copiers);
   k->block = 256;
-  set_args(*k, arena, arena + desc_off, n_desc, 0);
+  set_args(*k, arena, arena + desc_off, n_desc, n_items);
   k->entries = arena + entries_off;
-  k->n_args = 5;
+  k->corr_off = corr_off;
+  k->corr_bytes = corr_bytes;
+  k->host = host;
   return hipSuccess;
 }
 
@@ -284,12 +322,6 @@ hipError_t launch_to_planar(bool src_double, bool dst_double, const void* src, v
   else
     hipLaunchKernelGGL((to_planar<float, float>), grid, block, 0, s, (const float*)src, (float*)dst, nt, e);
   return hipGetLastError();
-}
-
-hipError_t launch_xsum(char* arena, int64_t desc_off, int64_t entries_off, int n_desc, hipStream_t s) {
-  KernelCall k;
-  const hipError_t e = xsum_call(arena, desc_off, entries_off, n_desc, &k);
-  return e != hipSuccess ? e : launch(k, s);
 }
 
 }  // namespace cdag

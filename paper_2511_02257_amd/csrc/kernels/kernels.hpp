@@ -11,8 +11,9 @@ namespace cdag {
 // launched on a stream or added to a graph as a kernel node.  Kernels take
 // (arena, descriptors, n_desc, n_items); the exterior contractions also
 // (trace descriptors, n_tdesc, n_titems) for the traces they may carry; the
-// cross sum takes (arena, descriptors, entries, n_desc).  bind() points args
-// at the fields; a copied KernelCall must be bound again.
+// cross sum (entries not null) takes (arena, descriptors, entries, n_desc,
+// n_items, corr_off, corr_bytes, host).  bind() points args at the fields; a
+// copied KernelCall must be bound again.
 struct KernelCall {
   const void* fn = nullptr;
   unsigned grid = 1, block = 1;
@@ -24,8 +25,9 @@ struct KernelCall {
   const void* tdesc = nullptr;
   int n_tdesc = 0;
   int64_t n_titems = 0;
-  int n_args = 4;
-  void* args[7] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+  int64_t corr_off = 0, corr_bytes = 0;
+  char* host = nullptr;
+  void* args[8] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   void bind();
 };
 hipError_t launch(KernelCall& k, hipStream_t s);
@@ -41,13 +43,16 @@ hipError_t hec_call(int prec, int variant, bool interior, char* arena, int64_t d
                     int64_t n_items, KernelCall* k, int64_t tdesc_off = 0, int n_tdesc = 0, int64_t n_titems = 0);
 hipError_t reduce_call(int prec, char* arena, int64_t desc_off, int n_desc, int64_t n_items, KernelCall* k);
 hipError_t hca_call(int prec, char* arena, int64_t desc_off, int n_desc, int64_t n_items, KernelCall* k);
-hipError_t xsum_call(char* arena, int64_t desc_off, int64_t entries_off, int n_desc, KernelCall* k);
+// Cross-diagram sums of n_items (correlator, t) pairs.  host: nullptr, or
+// pinned host memory that receives the corr_bytes of correlators at arena
+// offset corr_off and, after them, the sums (the arena's order).
+hipError_t xsum_call(char* arena, int64_t desc_off, int64_t entries_off, int n_desc, int64_t n_items,
+                     int64_t corr_off, int64_t corr_bytes, char* host, KernelCall* k);
 
 hipError_t launch_hec(int prec, int variant, bool interior, char* arena, int64_t desc_off, int n_desc,
                       int64_t n_items, hipStream_t s);
 hipError_t launch_reduce(int prec, char* arena, int64_t desc_off, int n_desc, int64_t n_items, hipStream_t s);
 hipError_t launch_hca(int prec, char* arena, int64_t desc_off, int n_desc, int64_t n_items, hipStream_t s);
-hipError_t launch_xsum(char* arena, int64_t desc_off, int64_t entries_off, int n_desc, hipStream_t s);
 // Kernel tables of the exterior contractions, one translation unit per
 // precision (hec_f64.hip, hec_f32.hip, hec_bf16x2.hip, hec_bf16x3.hip): the
 // kernel of tile `tile` (index into kTileShapes), `stages` LDS stages (1 or 2),

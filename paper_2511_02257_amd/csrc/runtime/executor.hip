@@ -102,7 +102,7 @@ struct Device {
   void* spill = nullptr;
   int64_t spill_bytes = 0;
   bool spill_pageable = false;
-  // pinned result buffer
+  // pinned result buffer, written by the cross-sum kernel
   void* results = nullptr;
   int64_t results_bytes = 0;
   // per step of every pass and per stream role; then per pass, the pass-end
@@ -121,6 +121,7 @@ struct Device {
   uint64_t graph_key = 0, graph_epoch = 0, graph_stage = 0;
   int graph_mode = 0;
   void* graph_spill = nullptr;
+  void* graph_results = nullptr;
 
   void drop_graphs() {
     for (auto g : seg_exec) ignore(hipGraphExecDestroy(g));
@@ -286,13 +287,15 @@ void ensure_spill(Device& D, int64_t need_bytes) {
   D.spill_bytes = need_bytes;
 }
 
+// Coherent, so that what a kernel stored there is seen by the host once the
+// stream has been waited for.
 void ensure_pinned(void*& p, int64_t& have, int64_t need_bytes) {
   if (have >= need_bytes && p) return;
   if (p) ignore(hipHostFree(p));
   p = nullptr;
   have = 0;
   if (need_bytes <= 0) return;
-  HIPC(hipHostMalloc(&p, (size_t)need_bytes, hipHostMallocDefault));
+  HIPC(hipHostMalloc(&p, (size_t)need_bytes, hipHostMallocMapped | hipHostMallocCoherent));
   have = need_bytes;
 }
 
@@ -305,6 +308,18 @@ hipError_t call_of(const Launch& L, int prec, char* arena, KernelCall* k) {
     case L_HCA: return hca_call(prec, arena, L.desc_off, L.n_desc, L.n_items, k);
     default: throw Error(CDAG_E_STATE, "bad launch type");
   }
+}
+
+// The last kernel of an execute: the cross sums, and the results to `host`.
+hipError_t finish_call(const KernelPlan& kp, char* arena, char* host, KernelCall* k) {
+  return xsum_call(arena, kp.xsum.desc_off, kp.xsum_entries_off, kp.xsum.n_desc, kp.xsum.n_items, kp.corr_off,
+                   kp.corr_bytes, host, k);
+}
+
+hipError_t launch_finish(const KernelPlan& kp, char* arena, char* host, hipStream_t st) {
+  KernelCall k;
+  const hipError_t e = finish_call(kp, arena, host, &k);
+  return e != hipSuccess ? e : launch(k, st);
 }
 
 hipError_t launch_one(const Launch& L, int prec, char* arena, hipStream_t st) {
@@ -616,25 +631,36 @@ struct GraphOps {
     HIPC(hipGraphAddMemcpyNode1D(&n, graph, deps.data(), deps.size(), dst, src, sz, kind));
     added(sr, n);
   }
+  void kernel(KernelCall& k) {
+    k.bind();
+    hipKernelNodeParams np{};
+    np.func = const_cast<void*>(k.fn);
+    np.gridDim = dim3(k.grid);
+    np.blockDim = dim3(k.block);
+    np.sharedMemBytes = 0;
+    np.kernelParams = k.args;
+    np.extra = nullptr;
+    deps_of(S_COMP);
+    hipGraphNode_t n = nullptr;
+    HIPC(hipGraphAddKernelNode(&n, graph, deps.data(), deps.size(), &np));
+    added(S_COMP, n);
+  }
   int64_t launch(int64_t g, const PassMap&) {
     const KernelPlan& kp = c.kplan;
     for (int64_t li = kp.launch_off[g]; li < kp.launch_off[g + 1]; ++li) {
       KernelCall k;
       HIPC(call_of(kp.launches[li], prec, D.arena, &k));
-      k.bind();
-      hipKernelNodeParams np{};
-      np.func = const_cast<void*>(k.fn);
-      np.gridDim = dim3(k.grid);
-      np.blockDim = dim3(k.block);
-      np.sharedMemBytes = 0;
-      np.kernelParams = k.args;
-      np.extra = nullptr;
-      deps_of(S_COMP);
-      hipGraphNode_t n = nullptr;
-      HIPC(hipGraphAddKernelNode(&n, graph, deps.data(), deps.size(), &np));
-      added(S_COMP, n);
+      kernel(k);
     }
     return kp.launch_off[g + 1] - kp.launch_off[g];
+  }
+  // the cross sums, after every stream's work
+  void finish() {
+    for (int r : {S_H2D, S_D2H})
+      if (hipGraphNode_t n = head(r)) pending[S_COMP].push_back(n);
+    KernelCall k;
+    HIPC(finish_call(c.kplan, D.arena, (char*)D.results, &k));
+    kernel(k);
   }
 };
 
@@ -827,12 +853,13 @@ void trace_execute(const Ctx& c, int prec, std::vector<cdag_trace_rec>& out, int
 
 namespace {
 // Capture global steps [g0, g1) into one graph on one stream (stream order
-// carries every dependency).
-hipGraph_t capture_steps(Ctx& c, Device& D, int prec, int64_t g0, int64_t g1) {
+// carries every dependency); the last segment ends with the cross sums.
+hipGraph_t capture_steps(Ctx& c, Device& D, int prec, int64_t g0, int64_t g1, bool last) {
   hipGraph_t g = nullptr;
   HIPC(hipStreamBeginCapture(D.cap, hipStreamCaptureModeThreadLocal));
   try {
     issue_steps(c, D, prec, g0, g1, D.cap, D.cap, D.cap, nullptr, true);
+    if (last) HIPC(launch_finish(c.kplan, D.arena, (char*)D.results, D.cap));
   } catch (...) {
     ignore(hipStreamEndCapture(D.cap, &g));
     if (g) ignore(hipGraphDestroy(g));
@@ -850,6 +877,7 @@ hipGraph_t build_graph(Ctx& c, Device& D, int prec) {
   try {
     GraphOps ops(c, D, prec, g);
     walk_steps(c, 0, c.plan.chunks() * (int64_t)c.plan.steps.size(), false, false, ops);
+    ops.finish();
   } catch (...) {
     ignore(hipGraphDestroy(g));
     throw;
@@ -907,19 +935,22 @@ void device_execute(Ctx& c, int prec, int batched, cdag_exec_stats* st) {
   D.tnext = 0;
   D.tpairs.clear();
   Device* timed = c.timing ? &D : nullptr;
+  const bool graphs = c.use_graphs && !c.timing && !D.spill_pageable;
   HIPC(hipEventRecord(D.t0, D.comp));
-  if (c.use_graphs && !c.timing && !D.spill_pageable) {
+  if (graphs) {
     // replay graphs: one-stream segments of kSegmentSteps steps when there are
-    // transfers (else one), or one graph built over the three streams
+    // transfers (else one), or one graph built over the three streams; the
+    // cross sums are the last one's last node (launched after the graphs they
+    // started 23 us after the last step's kernels)
     const bool one = c.use_graphs == 1;
     const int64_t seg = one && has_copies ? kSegmentSteps : std::max<int64_t>(G, 1);
     if (D.graph_key != pkey || D.graph_epoch != D.arena_epoch || D.graph_spill != D.spill ||
-        D.graph_stage != D.stage_version[prec] || D.graph_mode != c.use_graphs) {
+        D.graph_stage != D.stage_version[prec] || D.graph_mode != c.use_graphs || D.graph_results != D.results) {
       D.drop_graphs();
-      for (int64_t g0 = 0; g0 < G; g0 += seg) {
+      for (int64_t g0 = 0; g0 == 0 || g0 < G; g0 += seg) {
         hipGraph_t g = nullptr;
         try {
-          g = one ? capture_steps(c, D, prec, g0, std::min(G, g0 + seg)) : build_graph(c, D, prec);
+          g = one ? capture_steps(c, D, prec, g0, std::min(G, g0 + seg), g0 + seg >= G) : build_graph(c, D, prec);
         } catch (...) {
           D.drop_graphs();
           throw;
@@ -932,6 +963,7 @@ void device_execute(Ctx& c, int prec, int batched, cdag_exec_stats* st) {
       D.graph_key = pkey;
       D.graph_epoch = D.arena_epoch;
       D.graph_spill = D.spill;
+      D.graph_results = D.results;
       D.graph_stage = D.stage_version[prec];
       D.graph_mode = c.use_graphs;
     }
@@ -945,24 +977,22 @@ void device_execute(Ctx& c, int prec, int batched, cdag_exec_stats* st) {
     HIPC(hipEventRecord(D.ev_join[1], D.spill_s));
     HIPC(hipStreamWaitEvent(D.comp, D.ev_join[0], 0));
     HIPC(hipStreamWaitEvent(D.comp, D.ev_join[1], 0));
-  }
-  if (timed) {
-    hipEvent_t a = D.timing_event(), b = D.timing_event();
-    HIPC(hipEventRecord(a, D.comp));
-    HIPC(launch_xsum(D.arena, kp.xsum.desc_off, kp.xsum_entries_off, kp.xsum.n_desc, D.comp));
-    HIPC(hipEventRecord(b, D.comp));
-    D.tpairs.push_back({-1, 0, 0, -1, 0.0, a, b});
-  } else {
-    HIPC(launch_xsum(D.arena, kp.xsum.desc_off, kp.xsum_entries_off, kp.xsum.n_desc, D.comp));
+    hipEvent_t a = nullptr, b = nullptr;
+    if (timed) {
+      a = D.timing_event();
+      b = D.timing_event();
+      HIPC(hipEventRecord(a, D.comp));
+    }
+    HIPC(launch_finish(kp, D.arena, (char*)D.results, D.comp));
+    if (timed) {
+      HIPC(hipEventRecord(b, D.comp));
+      D.tpairs.push_back({-1, 0, 0, -1, 0.0, a, b});
+    }
   }
   n_launch++;
   HIPC(hipEventRecord(D.t1, D.comp));
-  if (kp.corr_bytes + kp.sums_bytes > 0)
-    HIPC(hipMemcpyAsync(D.results, D.arena + kp.corr_off, (size_t)(kp.corr_bytes + kp.sums_bytes),
-                        hipMemcpyDeviceToHost, D.comp));
+  // the compute stream follows every transfer and the results are on the host
   HIPC(hipStreamSynchronize(D.comp));
-  HIPC(hipStreamSynchronize(D.copy));
-  HIPC(hipStreamSynchronize(D.spill_s));
   float ms = 0;
   HIPC(hipEventElapsedTime(&ms, D.t0, D.t1));
   c.corr_host.assign((const double*)D.results, (const double*)D.results + kp.corr_bytes / 8);
@@ -1073,7 +1103,7 @@ void device_execute_static(Ctx& c, int prec, cdag_exec_stats* st) {
     for (int64_t u = 0; u < c.dag.n_leaves; ++u) ops.upload_leaf(u, p.leaf_off[u]);
   const int64_t G = (int64_t)p.steps.size();
   int64_t n_launch = walk_steps(c, 0, G, true, false, ops);
-  HIPC(launch_xsum(base, kp.xsum.desc_off, kp.xsum_entries_off, kp.xsum.n_desc, s));
+  HIPC(launch_finish(kp, base, nullptr, s));
   ++n_launch;
   HIPC(hipMemcpyAsync(c.corr_host.data(), base + kp.corr_off, (size_t)kp.corr_bytes, hipMemcpyDeviceToHost, s));
   HIPC(hipMemcpyAsync(c.sums_host.data(), base + kp.sums_off, (size_t)kp.sums_bytes, hipMemcpyDeviceToHost, s));

@@ -88,6 +88,23 @@ CDAG_OCCUPANCY(1, Tile4, 2, 4)
 CDAG_OCCUPANCY(2, Tile0, 1, 3)
 CDAG_OCCUPANCY(2, Tile3, 1, 2)
 #undef CDAG_OCCUPANCY
+// The ragged form keeps more registers live (it also holds the products of a
+// wave's edge blocks): the one target it would miss by spilling is lowered.
+template <int P, class TL, int ST, bool PF, bool RAG>
+constexpr int occupancy_waves() {
+  return RAG && P == 0 && TL::NTH == 256 && TL::BM * TL::BN == 4096 && ST == 1 && !PF ? 2
+                                                                                     : Occupancy<P, TL, ST, PF>::waves;
+}
+
+// Compile-time integers and loops over them.
+template <int I> struct Int { static constexpr int value = I; };
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (N > 0) {
+    static_for<N - 1>(f);
+    f(Int<N - 1>{});
+  }
+}
 
 struct WorkItem {
   const HecDesc* h;
@@ -206,6 +223,9 @@ template <> struct Vec2<float> { typedef float4 V; static constexpr int n = 4; }
 template <typename T> struct Vec16;
 template <> struct Vec16<double> { typedef double V __attribute__((ext_vector_type(2))); };
 template <> struct Vec16<float> { typedef float V __attribute__((ext_vector_type(4))); };
+// The same 16 bytes at any element's address (rows of odd length): the memory
+// unit takes a 16-byte load at 4-byte alignment.
+template <typename T> struct Vec16U { typedef typename Vec16<T>::V V __attribute__((aligned(sizeof(T)))); };
 
 // Wait for every vector memory operation of this wave (s_waitcnt vmcnt(0);
 // expcnt and lgkmcnt left free).  Called where the loaded k-slice is stored to
@@ -237,25 +257,6 @@ __device__ __forceinline__ void load8(T (&r)[8], const T* src, int valid, bool v
   } else {
 #pragma unroll
     for (int i = 0; i < 8; ++i) r[i] = i < valid ? src[i] : T(0);
-  }
-}
-
-// One 16-byte chunk (W = 16 / sizeof(T) elements) of a row: a vector load when
-// all W are in range and rows are W-element aligned, otherwise element-wise
-// with zero fill.
-template <typename T>
-__device__ __forceinline__ void load16b(T (&r)[16 / sizeof(T)], const T* src, int valid, bool vec) {
-  constexpr int W = 16 / (int)sizeof(T);
-  typedef typename Vec2<T>::V V;
-  static_assert(sizeof(V) == 16, "one vector per chunk");
-  if (vec && valid == W) {
-    V v = *reinterpret_cast<const V*>(src);
-    const T* e = reinterpret_cast<const T*>(&v);
-#pragma unroll
-    for (int i = 0; i < W; ++i) r[i] = e[i];
-  } else {
-#pragma unroll
-    for (int i = 0; i < W; ++i) r[i] = i < valid ? src[i] : T(0);
   }
 }
 
@@ -512,7 +513,7 @@ __device__ __forceinline__ void store_block(T* C, int M, int N, int row0, int co
 // contractions' work items (one workgroup per item; trace_block); without TR
 // the last three arguments are unused.
 template <typename T, class TL, int ST, bool PF, bool GEN = false, bool FULL = false, bool TR = false>
-__global__ void __launch_bounds__(TL::NTH, (Occupancy<sizeof(T) == 8 ? 0 : 1, TL, ST, PF>::waves))
+__global__ void __launch_bounds__(TL::NTH, (occupancy_waves<sizeof(T) == 8 ? 0 : 1, TL, ST, PF, !FULL && !GEN>()))
 hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc, int64_t n_items,
          const HcaDesc* __restrict__ tdescs, int n_tdesc, int64_t n_titems) {
   static_assert(!(GEN && FULL), "a general contraction is never interior");
@@ -545,10 +546,17 @@ hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
   T (&As)[ST][2][BM][APAD] = *reinterpret_cast<T (*)[ST][2][BM][APAD]>(smem);            // [stage][plane][m][k]
   T (&Bs)[ST][2][BK][BPAD] = *reinterpret_cast<T (*)[ST][2][BK][BPAD]>(smem + A_ELEMS);  // [stage][plane][k][n]
   T (&Cs)[2][BM][CPAD] = *reinterpret_cast<T (*)[2][BM][CPAD]>(smem);                   // [plane][m][n]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // RAG: a ragged launch.  A wave skips the 16 x 16 blocks that lie outside
+  // M x N and the 4-deep k steps past the k range; the waves' places in the
+  // tile turn with the workgroup, so that the places with fewer blocks fall on
+  // every SIMD alike.
+  constexpr bool RAG = !FULL && !GEN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(RAG ? ((tid >> 6) + (int)blockIdx.x) % (NTH / 64) : tid >> 6);
   const int wm = wave / TL::WGN, wn = wave % TL::WGN, li = lane & 15, lk = lane >> 4;
 
   typedef typename Vec16<T>::V VL;
+  typedef typename Vec16U<T>::V VU;
   constexpr int NA = 8 / W;     // 16-byte tuples per A segment
   VL ra[LA][NA], rb[LB];
   auto gload = [&](const ItemView<T>& o, int k0) {
@@ -577,30 +585,57 @@ hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
       }
       return;
     }
-    // ragged or general: element-wise where a row or k range ends
+    if constexpr (!GEN) {
+      // Ragged: the same 16-byte loads at any alignment, with no mask.  Rows
+      // past M repeat row M - 1 and columns past N take what follows the row:
+      // their products reach only outputs that are not stored.  Elements past
+      // the k range are zeroed on their way to LDS (sstore).  A segment that
+      // starts past a row's or the k range's end loads the range's start
+      // instead, so a load ends at most 7 elements (56 bytes) past its tensor,
+      // which the arena always holds (descriptor tables and results follow
+      // every tensor).  Element-wise loads behind one test each were the bound
+      // before: FP64 K22 at N = 45 18 -> 21 TFLOP/s and FP32 at N = 48 25 -> 33
+      // on the default tiles (66 on the one-stage 64 x 64 one), FP64 C1..C3 at
+      // N = 24 20 -> 25, bits unchanged.
+#pragma unroll
+      for (int q = 0; q < LA; ++q) {
+        const int seg = tid + q * NTH;
+        if (SEGA % NTH == 0 || seg < SEGA) {
+          const int p = seg / (SPR * BM), r = (seg % (SPR * BM)) / SPR, hh = seg % SPR;
+          const int am = min(o.m0 + r, o.M - 1), ak = k0 + 8 * hh < o.kend ? k0 + 8 * hh : o.kbeg;
+          const T* src = o.A + ((int64_t)p * o.M + am) * o.K + ak;
+#pragma unroll
+          for (int j = 0; j < NA; ++j) ra[q][j] = *reinterpret_cast<const VU*>(src + W * j);
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < LB; ++q) {
+        const int seg = tid + q * NTH;
+        if (SEGB % NTH == 0 || seg < SEGB) {
+          const int p = seg / (BK * (BN / W)), rem = seg % (BK * (BN / W));
+          const int kk = rem / (BN / W), cw = rem % (BN / W);
+          const int bk = min(k0 + kk, o.kend - 1), bn = o.n0 + W * cw < o.N ? o.n0 + W * cw : o.n0;
+          rb[q] = *reinterpret_cast<const VU*>(o.B + ((int64_t)p * o.K + bk) * o.N + bn);
+        }
+      }
+      return;
+    }
+    // general: element by element through the index map
 #pragma unroll
     for (int q = 0; q < LA; ++q) {
       const int seg = tid + q * NTH;
       if (SEGA % NTH == 0 || seg < SEGA) {
         const int p = seg / (SPR * BM), r = (seg % (SPR * BM)) / SPR, hh = seg % SPR;
         const int am = o.m0 + r, ak = k0 + 8 * hh;
-        T e[8];
-        if constexpr (GEN) {
-          const IndexMap& mp = *o.map;
-          const T* plane = o.A + (int64_t)p * o.M * o.K;
-          const int64_t row = am < o.M ? digit_offset(am, mp.dm, mp.n, mp.a_m) : 0;
+        const IndexMap& mp = *o.map;
+        const T* plane = o.A + (int64_t)p * o.M * o.K;
+        const int64_t row = am < o.M ? digit_offset(am, mp.dm, mp.n, mp.a_m) : 0;
 #pragma unroll
-          for (int i = 0; i < 8; ++i)
-            e[i] = (am < o.M && ak + i < o.kend) ? plane[row + digit_offset(ak + i, mp.dk, mp.n, mp.a_k)] : T(0);
-        } else {
-          const int av = am < o.M ? max(0, min(8, o.kend - ak)) : 0;
-          load8<T>(e, o.A + (int64_t)p * o.M * o.K + (int64_t)am * o.K + ak, av, o.avec);
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) ra[q][i / W][i % W] = e[i];
+        for (int i = 0; i < 8; ++i)
+          ra[q][i / W][i % W] =
+              (am < o.M && ak + i < o.kend) ? plane[row + digit_offset(ak + i, mp.dk, mp.n, mp.a_k)] : T(0);
       }
     }
-    const bool bvw = (o.N % W) == 0;
 #pragma unroll
     for (int q = 0; q < LB; ++q) {
       const int seg = tid + q * NTH;
@@ -608,25 +643,33 @@ hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
         const int p = seg / (BK * (BN / W)), rem = seg % (BK * (BN / W));
         const int kk = rem / (BN / W), cw = rem % (BN / W);
         const int bkk = k0 + kk, bn = o.n0 + W * cw;
-        T e[W];
-        if constexpr (GEN) {
-          const IndexMap& mp = *o.map;
-          const T* plane = o.B + (int64_t)p * o.K * o.N;
-          const int64_t row = bkk < o.kend ? digit_offset(bkk, mp.dk, mp.n, mp.b_k) : 0;
+        const IndexMap& mp = *o.map;
+        const T* plane = o.B + (int64_t)p * o.K * o.N;
+        const int64_t row = bkk < o.kend ? digit_offset(bkk, mp.dk, mp.n, mp.b_k) : 0;
 #pragma unroll
-          for (int i = 0; i < W; ++i)
-            e[i] = (bkk < o.kend && bn + i < o.N) ? plane[row + digit_offset(bn + i, mp.dn, mp.n, mp.b_n)] : T(0);
-        } else {
-          const int bv = bkk < o.kend ? max(0, min(W, o.N - bn)) : 0;
-          load16b<T>(e, o.B + (int64_t)p * o.K * o.N + (int64_t)bkk * o.N + bn, bv, bvw);
-        }
-#pragma unroll
-        for (int i = 0; i < W; ++i) rb[q][i] = e[i];
+        for (int i = 0; i < W; ++i)
+          rb[q][i] = (bkk < o.kend && bn + i < o.N) ? plane[row + digit_offset(bn + i, mp.dn, mp.n, mp.b_n)] : T(0);
       }
     }
   };
-  auto sstore = [&](int st) {
+  // left: k elements of the loaded slice and those after it (RAG: the slice's
+  // elements from `left` on are stored as zeros)
+  auto sstore = [&](int st, int left) {
     wait_loads();
+    if (RAG && left < BK) {
+#pragma unroll
+      for (int q = 0; q < LA; ++q) {
+        const int hh = (tid + q * NTH) % SPR;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (8 * hh + i >= left) ra[q][i / W][i % W] = T(0);
+      }
+#pragma unroll
+      for (int q = 0; q < LB; ++q) {
+        const int kk = ((tid + q * NTH) % (BK * (BN / W))) / (BN / W);
+        if (kk >= left) rb[q] = VL{};
+      }
+    }
 #pragma unroll
     for (int q = 0; q < LA; ++q) {
       const int seg = tid + q * NTH;
@@ -682,52 +725,79 @@ hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
         p3[i][j] = V{0, 0, 0, 0};
       }
 
-    // One k-slice of products from LDS stage st.
-    auto mma_slice = [&](int st) {
+    // Products of the 4-deep k step k4 in LDS stage st, for the wave's first
+    // VI x VJ blocks.
+    auto mma_step = [&](auto vi_, auto vj_, int st, int k4) {
+      constexpr int VI = decltype(vi_)::value, VJ = decltype(vj_)::value;
+      const int kk = 4 * k4 + lk;
+      T a_r[VI], a_i[VI], b_r[VJ], b_i[VJ];
 #pragma unroll
-      for (int k4 = 0; k4 < BK / 4; ++k4) {
-        const int kk = 4 * k4 + lk;
-        T a_r[TM], a_i[TM], b_r[TN], b_i[TN];
+      for (int i = 0; i < VI; ++i) {
+        a_r[i] = As[st][0][(wm * TM + i) * 16 + li][kk];
+        a_i[i] = As[st][1][(wm * TM + i) * 16 + li][kk];
+      }
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          a_r[i] = As[st][0][(wm * TM + i) * 16 + li][kk];
-          a_i[i] = As[st][1][(wm * TM + i) * 16 + li][kk];
-        }
+      for (int j = 0; j < VJ; ++j) {
+        b_r[j] = Bs[st][0][kk][(wn * TN + j) * 16 + li];
+        b_i[j] = Bs[st][1][kk][(wn * TN + j) * 16 + li];
+      }
+      if constexpr (G3) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          b_r[j] = Bs[st][0][kk][(wn * TN + j) * 16 + li];
-          b_i[j] = Bs[st][1][kk][(wn * TN + j) * 16 + li];
-        }
-        if constexpr (G3) {
+        for (int i = 0; i < VI; ++i)
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
+          for (int j = 0; j < VJ; ++j) {
+            p1[i][j] = Mfma<T>::mma(a_r[i], b_r[j], p1[i][j]);
+            p2[i][j] = Mfma<T>::mma(a_i[i], b_i[j], p2[i][j]);
+            p3[i][j] = Mfma<T>::mma(a_r[i] + a_i[i], b_r[j] + b_i[j], p3[i][j]);
+          }
+      } else {
+        T b_n[VJ];
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-              p1[i][j] = Mfma<T>::mma(a_r[i], b_r[j], p1[i][j]);
-              p2[i][j] = Mfma<T>::mma(a_i[i], b_i[j], p2[i][j]);
-              p3[i][j] = Mfma<T>::mma(a_r[i] + a_i[i], b_r[j] + b_i[j], p3[i][j]);
+        for (int j = 0; j < VJ; ++j) b_n[j] = -b_i[j];
+        // Consecutive instructions go to different accumulators; each
+        // accumulator still adds its two products in the same order.
+#pragma unroll
+        for (int i = 0; i < VI; ++i)
+#pragma unroll
+          for (int j = 0; j < VJ; ++j) {
+            p1[i][j] = Mfma<T>::mma(a_r[i], b_r[j], p1[i][j]);
+            p3[i][j] = Mfma<T>::mma(a_r[i], b_i[j], p3[i][j]);
+          }
+#pragma unroll
+        for (int i = 0; i < VI; ++i)
+#pragma unroll
+          for (int j = 0; j < VJ; ++j) {
+            p1[i][j] = Mfma<T>::mma(a_i[i], b_n[j], p1[i][j]);
+            p3[i][j] = Mfma<T>::mma(a_i[i], b_r[j], p3[i][j]);
+          }
+      }
+    };
+    // the wave's blocks inside M x N (RAG)
+    const int vi = RAG ? max(0, min(TM, (cur.M - cur.m0 + 15) / 16 - wm * TM)) : TM;
+    const int vj = RAG ? max(0, min(TN, (cur.N - cur.n0 + 15) / 16 - wn * TN)) : TN;
+    // One k-slice of products from LDS stage st, of which `left` elements of k
+    // remain.  Whole slices run unrolled for the wave's number of blocks.
+    auto mma_slice = [&](int st, int left) {
+      if constexpr (!RAG) {
+#pragma unroll
+        for (int k4 = 0; k4 < BK / 4; ++k4) mma_step(Int<TM>{}, Int<TN>{}, st, k4);
+      } else {
+        const int n4 = min(BK / 4, (left + 3) / 4);
+        static_for<TM>([&](auto i_) {
+          static_for<TN>([&](auto j_) {
+            typedef Int<decltype(i_)::value + 1> VI;
+            typedef Int<decltype(j_)::value + 1> VJ;
+            if (vi == VI::value && vj == VJ::value) {
+              if (n4 == BK / 4) {
+#pragma unroll
+                for (int k4 = 0; k4 < BK / 4; ++k4) mma_step(VI{}, VJ{}, st, k4);
+              } else {
+#pragma unroll 1
+                for (int k4 = 0; k4 < n4; ++k4) mma_step(VI{}, VJ{}, st, k4);
+              }
             }
-        } else {
-          T b_n[TN];
-#pragma unroll
-          for (int j = 0; j < TN; ++j) b_n[j] = -b_i[j];
-          // Consecutive instructions go to different accumulators; each
-          // accumulator still adds its two products in the same order.
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-              p1[i][j] = Mfma<T>::mma(a_r[i], b_r[j], p1[i][j]);
-              p3[i][j] = Mfma<T>::mma(a_r[i], b_i[j], p3[i][j]);
-            }
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-              p1[i][j] = Mfma<T>::mma(a_i[i], b_n[j], p1[i][j]);
-              p3[i][j] = Mfma<T>::mma(a_i[i], b_r[j], p3[i][j]);
-            }
-        }
+          });
+        });
       }
     };
     // Each slice but the last loads the next one while its products run; the
@@ -735,37 +805,37 @@ hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
     // off so that every pass of the loop stores what it loaded: no load is in
     // flight when the loop comes round, and the compiler has no reason to wait
     // for the prefetch before the products.
-    const int nk = (cur.kend - cur.kbeg + BK - 1) / BK;
+    const int klen = cur.kend - cur.kbeg, nk = (klen + BK - 1) / BK;
     int c = 0;
     if (ST == 2) {
-      sstore(0);
+      sstore(0, klen);
       __syncthreads();
       for (; c + 1 < nk; ++c) {
         gload(cur, cur.kbeg + (c + 1) * BK);
         fence();
-        mma_slice(c & 1);
+        mma_slice(c & 1, BK);
         fence();
-        sstore((c & 1) ^ 1);
+        sstore((c & 1) ^ 1, klen - (c + 1) * BK);
         __syncthreads();
       }
     } else {
       for (; c + 1 < nk; ++c) {
-        sstore(0);
+        sstore(0, BK);
         __syncthreads();
         gload(cur, cur.kbeg + (c + 1) * BK);
         fence();
-        mma_slice(0);
+        mma_slice(0, BK);
         __syncthreads();
       }
       if (nk > 0) {
-        sstore(0);
+        sstore(0, klen - c * BK);
         __syncthreads();
       }
     }
     if (PF && has_next) gload(nxt, nxt.kbeg);
     fence();
     if (nk > 0) {
-      mma_slice(ST == 2 ? (c & 1) : 0);
+      mma_slice(ST == 2 ? (c & 1) : 0, klen - c * BK);
       __syncthreads();
     }
 
@@ -780,6 +850,7 @@ hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
+        if (RAG && (i >= vi || j >= vj)) continue;
         V re = p1[i][j], im = p3[i][j];
         if constexpr (G3) {
 #pragma unroll

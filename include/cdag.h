@@ -399,7 +399,10 @@ int cdag_launch_records(cdag_ctx* c, cdag_launch_record* out, int64_t cap, int64
  * cut into K splits summed by a fixed-order reduction; 0 = never split (one
  * work item per output tile, the whole K in one accumulator).
  * Without an explicit choice a default by N applies (split_k 1;
- * cdag_get_tile reports the choice in force).  Every choice gives results
+ * cdag_get_tile reports it): its product form and its K splits, on the tile of
+ * that form that suits the contraction's GEMM, with one LDS stage (launch
+ * records report the variant that ran; variant 30 is a 128x128 tile of 512
+ * threads, split BF16 only).  Every choice gives results
  * within the precision's bound; bits may differ between choices, never with
  * the grouping of contractions into launches. */
 int cdag_set_tile(cdag_ctx* c, int prec, int kind, int nvec, int tile, int grid, int lds_stages,

@@ -103,6 +103,43 @@ void decompose(const Gemm& g, int nt, int choice, int prec, HecDesc* h, int nt_r
   h->tile_count = (int32_t)((int64_t)h->nt * h->tiles_m * h->tiles_n * splits);
 }
 
+// Cut h into the output tiles of variant v (its K splits stay).
+static void retile(int v, HecDesc* h) {
+  const TileShape& ts = kTileShapes[variant_tile(v)];
+  h->tiles_m = (h->M + ts.bm - 1) / ts.bm;
+  h->tiles_n = (h->N + ts.bn - 1) / ts.bn;
+  h->tile_count = (int32_t)((int64_t)h->nt * h->tiles_m * h->tiles_n * h->splits);
+}
+
+// Every tile of one product form gives the same bits (each output adds its
+// products in the same order), so without an explicit choice the tile follows
+// the GEMM.  All with one LDS stage: it leaves room for more workgroups per
+// compute unit, and no size measured was faster with two (FP64 K22 at N = 64
+// 685 -> 623 us, FP32 K33 572 -> 502, split BF16 K22 at N = 48 337 -> 172).
+// Measured (us, waves of one kind, Nt 8 to 32; N and M: the GEMM's):
+//   three products (N <= 32): 32 x 32, but 64 x 32 from M = 64 on (K32 at N =
+//     32: FP64 119 -> 102, FP32 68 -> 59; K22, M = 32: 130 against 184);
+//   four products: 64 x 64, or 48 x 48 where N fills its tiles better (FP64 K33
+//     at N = 72 2860 -> 2338, 96 7533 -> 5134, FP32 K22 at 96 1563 -> 1180; at
+//     64 964 against 1389), to N = 64 only for long K (FP64 K33 at N = 48
+//     450 -> 368; K22, K = N: FP32 at 48 240 against 279, FP64 at 45 540
+//     against 620);
+//   split BF16 (one form on every tile): to N = 32 as three products; to 64 the
+//     64 x 64 tile (K22 at N = 48, two pieces: 172 against 207 and more); above,
+//     128 x 64 with two pieces (K33 at N = 96 1467 -> 1393, 128 912 -> 774) and
+//     128 x 128 with three (1443 -> 1138 at 128), which split each operand
+//     value fewer times.
+int default_variant(int prec, int variant, const Gemm& g) {
+  const bool bf16 = prec >= 2, gauss = !bf16 && variant_tile(variant) == 1;
+  if (gauss || (bf16 && g.N <= 32)) return variant_of(g.M >= 64 ? 4 : 1, 1, 1);
+  if (bf16) {
+    if (g.N <= 64) return variant_of(0, 1, 1);
+    return prec == 2 ? variant_of(3, 1, 1) : kExtraVariantId;
+  }
+  const bool fits48 = (g.N + 47) / 48 * 48 < (g.N + 63) / 64 * 64;
+  return variant_of(fits48 && (g.N > 64 || g.K >= 512) ? 2 : 0, 1, 1);
+}
+
 int default_tile(int prec, int kind, int n) {
   (void)prec;
   (void)kind;
@@ -157,10 +194,16 @@ KernelPlan make_kernel_plan(const Dag& d, const Plan& p, int prec, const TileTab
   // A pass covers nt / t_chunks slices; the split count follows the whole
   // contraction (all nt slices), so it does not change with t_chunks and the
   // results stay bit-identical.
-  auto decomp = [&](int64_t u, HecDesc& h) {
+  auto decomp = [&](int64_t u, HecDesc& h) -> int {
     Gemm g;
     d.gemm_shape(u, &g.M, &g.N, &g.K);
-    decompose(g, d.nt[u], tile_of(u), prec, &h, (int)(d.nt[u] / p.chunks()));
+    const int choice = tile_of(u);
+    decompose(g, d.nt[u], choice, prec, &h, (int)(d.nt[u] / p.chunks()));
+    if (is_spec(d.kind[u])) return kGenVariant;
+    if (tiles.count(std::make_tuple(prec, (int)d.kind[u], (int)d.nvec[u]))) return choice_variant(choice);
+    const int v = default_variant(prec, choice_variant(choice), g);
+    retile(v, &h);
+    return v;
   };
 
   // pass 1: workspace size (max over steps) and descriptor counts
@@ -196,7 +239,7 @@ KernelPlan make_kernel_plan(const Dag& d, const Plan& p, int prec, const TileTab
     for (int64_t s = 0; s < S; ++s) {
       const size_t step_first = kp.launches.size();
       kp.launch_off.push_back((int64_t)kp.launches.size());
-      constexpr int kGroups = kNumVariants + 1;   // the variants, then the general kernel
+      constexpr int kGroups = kAllVariants;
       std::vector<HecDesc> hec[kGroups];
       int64_t tiles[kGroups] = {0};
       double v_flops[kGroups] = {0}, v_bytes[kGroups] = {0};
@@ -236,9 +279,8 @@ KernelPlan make_kernel_plan(const Dag& d, const Plan& p, int prec, const TileTab
           continue;
         }
         HecDesc h{};
-        decomp(u, h);
-        const bool gen = is_spec(d.kind[u]);
-        const int tl = gen ? kGenVariant : choice_variant(tile_of(u));
+        const int tl = decomp(u, h);
+        const bool gen = tl == kGenVariant;
         h.map_off = -1;
         if (gen) {
           const auto key = std::make_pair(d.kind[u], d.nvec[u]);

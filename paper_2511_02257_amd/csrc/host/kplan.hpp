@@ -42,9 +42,6 @@ constexpr int kNumGrids = 2, kNumVariants = kNumTiles * kNumGrids * 2;
 inline int variant_of(int tile, int grid, int stages = 2) {
   return tile + kNumTiles * (grid + 2 * (2 - stages));
 }
-inline int variant_tile(int v) { return v % kNumTiles; }
-inline int variant_grid(int v) { return (v / kNumTiles) % 2; }
-inline int variant_stages(int v) { return 2 - v / (2 * kNumTiles); }
 // A kernel choice is a variant plus the split-K mode:
 // choice = variant + kNumVariants * (split-K allowed ? 0 : 1).  Split-K, when
 // allowed, follows the per-contraction rule of decompose(); either way the
@@ -61,7 +58,7 @@ inline int choice_of(int variant, bool split_k) { return variant + kNumVariants 
 inline int choice_variant(int c) { return c % kNumVariants; }
 inline bool choice_split_k(int c) { return c < kNumVariants; }
 // Choice per (precision, kind, N): an explicit table entry (set through the
-// ABI or by the autotuner) wins, else default_tile().
+// ABI or by the autotuner) wins, else default_tile(), run by default_variant().
 using TileTable = std::map<std::tuple<int, int, int>, int>;
 int default_tile(int prec, int kind, int n);   // returns a choice
 // Complex GEMM per time slice of an exterior contraction (Dag::gemm_shape).
@@ -71,6 +68,10 @@ struct Gemm { int64_t M, N, K; };
 // the descriptor covers nt_run of the nt slices (one pass of a time-chunked
 // execution); the split count still follows all nt.
 void decompose(const Gemm& g, int nt, int choice, int prec, HecDesc* h, int nt_run = 0);
+// Variant that runs a contraction with GEMM g (per time slice) where no choice
+// was made; variant: default_tile()'s, which fixes the product form (three or
+// four products in FP64 and FP32) and, through decompose(), the K splits.
+int default_variant(int prec, int variant, const Gemm& g);
 // Distinct (kind, N) among the exterior contractions of d (the keys of the
 // kernel-choice table), each with its largest Nt and its largest GEMM (a
 // general kind can occur with several operand ranks).

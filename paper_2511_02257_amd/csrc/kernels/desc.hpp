@@ -16,23 +16,34 @@
 namespace cdag {
 
 // Exterior-contraction tile shapes (workgroup output tile BM x BN, threads).
-// The kernels instantiate exactly these, in this order.
+// The kernels instantiate exactly these, in this order.  The first kNumTiles
+// can be chosen (cdag_set_tile); the last runs only where no choice was made,
+// in split BF16.
 struct TileShape { int32_t bm, bn, nth; };
-constexpr int kNumTiles = 6;
-constexpr TileShape kTileShapes[kNumTiles] = {
-    {64, 64, 256}, {32, 32, 256}, {48, 48, 64}, {128, 64, 256}, {64, 32, 256}, {64, 64, 512}};
+constexpr int kNumTiles = 6, kAllTiles = 7;
+constexpr TileShape kTileShapes[kAllTiles] = {{64, 64, 256}, {32, 32, 256}, {48, 48, 64},   {128, 64, 256},
+                                              {64, 32, 256}, {64, 64, 512}, {128, 128, 512}};
 
-// Launch variant of the general kernel (contractions over any index pairs):
-// one past the tile x grid x stages variants.
+// Launch variant: tile + kNumTiles * (grid + 2 * (2 - stages)) for the tiles
+// that can be chosen, then the general kernel (contractions over any index
+// pairs), then kExtraVariantId + kNumTiles * (tile - kNumTiles) for the other
+// tile (one LDS stage, one workgroup per item).
 constexpr int kGenVariantId = 4 * kNumTiles;
+constexpr int kExtraVariantId = 5 * kNumTiles;
+constexpr int variant_tile(int v) {
+  return v < kGenVariantId ? v % kNumTiles : kNumTiles + (v - kExtraVariantId) / kNumTiles;
+}
+constexpr int variant_grid(int v) { return v < kGenVariantId ? (v / kNumTiles) % 2 : 1; }
+constexpr int variant_stages(int v) { return v < 2 * kNumTiles ? 2 : 1; }
+constexpr int kAllVariants = kExtraVariantId + kNumTiles * (kAllTiles - kNumTiles);
 
 // Most workgroups in one launch; a launch with more work items strides.
 constexpr int64_t kMaxGrid = 1 << 20;
 // Root traces that one workgroup of `nth` threads takes when an exterior-
-// contraction launch carries its step's traces (a group of four waves per
-// trace; a 64-thread workgroup takes one as a single wave), and the
+// contraction launch carries its step's traces (one per group of four waves,
+// or one per wave where the waves are no whole groups of four), and the
 // workgroups that n of them need.
-constexpr int traces_per_block(int nth) { return nth >= 256 ? nth / 256 : 1; }
+constexpr int traces_per_block(int nth) { return nth % 256 == 0 ? nth / 256 : nth / 64; }
 constexpr int64_t trace_blocks(int nth, int64_t n) {
   return (n + traces_per_block(nth) - 1) / traces_per_block(nth);
 }

@@ -59,6 +59,8 @@ typedef Tile<1, 1, 3, 3> Tile2;   //  48 x 48,  64 threads
 typedef Tile<2, 2, 4, 2> Tile3;   // 128 x 64, 256 threads
 typedef Tile<2, 2, 2, 1> Tile4;   //  64 x 32, 256 threads
 typedef Tile<2, 4, 2, 1> Tile5;   //  64 x 64, 512 threads (half the accumulators per wave)
+// Split BF16 without a choice only: one LDS stage, one workgroup per item.
+typedef Tile<2, 4, 4, 2> Tile6;   // 128 x 128, 512 threads
 
 // Occupancy target of an exterior-contraction kernel: the waves per SIMD that
 // its register budget must allow (the compiler keeps each lane within
@@ -152,7 +154,6 @@ struct ItemView {
   const T* A;
   const T* B;
   int M, N, K, t, sp, m0, n0, kbeg, kend;
-  bool avec;         // rows of A allow 8-element vector loads
   const IndexMap* map;   // a contraction over any index pairs, else nullptr
 };
 
@@ -187,7 +188,6 @@ __device__ __forceinline__ ItemView<T> view_item(char* arena, const HecDesc* des
   v.A = reinterpret_cast<const T*>(arena + w.h->a_off) + (int64_t)w.t * 2 * v.M * v.K;
   v.B = reinterpret_cast<const T*>(arena + w.h->b_off) + (int64_t)w.t * 2 * v.K * v.N;
   v.map = w.h->map_off >= 0 ? reinterpret_cast<const IndexMap*>(arena + w.h->map_off) : nullptr;
-  v.avec = (v.K & 7) == 0 && v.map == nullptr;
   return v;
 }
 
@@ -227,6 +227,10 @@ template <> struct Vec16<float> { typedef float V __attribute__((ext_vector_type
 // unit takes a 16-byte load at 4-byte alignment.
 template <typename T> struct Vec16U { typedef typename Vec16<T>::V V __attribute__((aligned(sizeof(T)))); };
 
+// V at its own alignment, or at a float's.
+template <typename V_, bool OWN> struct Aligned { typedef V_ V; };
+template <typename V_> struct Aligned<V_, false> { typedef V_ V __attribute__((aligned(4))); };
+
 // Wait for every vector memory operation of this wave (s_waitcnt vmcnt(0);
 // expcnt and lgkmcnt left free).  Called where the loaded k-slice is stored to
 // LDS, which needs it anyway: past this point no load is in flight on any
@@ -238,27 +242,6 @@ __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70
 // otherwise sink them next to their LDS store, exposing their latency) and
 // the LDS store behind them.
 __device__ __forceinline__ void fence() { __builtin_amdgcn_sched_barrier(0); }
-
-// 8 consecutive elements of one row: vector loads when fully in range and the
-// row is 8-element aligned, otherwise element-wise with zero fill.
-template <typename T>
-__device__ __forceinline__ void load8(T (&r)[8], const T* src, int valid, bool vec) {
-  if (vec && valid == 8) {
-    typedef typename Vec2<T>::V V;
-    constexpr int W = Vec2<T>::n;
-    const V* s = reinterpret_cast<const V*>(src);
-#pragma unroll
-    for (int q = 0; q < 8 / W; ++q) {
-      V v = s[q];
-      const T* e = reinterpret_cast<const T*>(&v);
-#pragma unroll
-      for (int i = 0; i < W; ++i) r[q * W + i] = e[i];
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) r[i] = i < valid ? src[i] : T(0);
-  }
-}
 
 // ------------------------------------------------------------------ root traces
 // K consecutive elements of one row (K = 2 or 4): WHOLE, vector loads from a
@@ -453,22 +436,22 @@ __device__ __forceinline__ void trace_group(char* arena, const HcaDesc* descs, i
 // Traces carried by an exterior-contraction launch (the traces of the same
 // plan step, which read only earlier steps' outputs): block b after the
 // contractions' work items takes traces b * G .. b * G + G - 1, G = NTH / 256
-// (traces_per_block) in the workgroup layout, or one in the wave layout for
-// 64-thread tiles; blocks load in halves, so that the trace path needs no
-// more registers than the contractions do.
+// (traces_per_block) in the workgroup layout, or one per wave in the wave
+// layout where the waves are no whole groups of four; blocks load in halves, so
+// that the trace path needs no more registers than the contractions do.
 template <typename T, int NTH>
 __device__ __forceinline__ void trace_block(char* arena, const HcaDesc* descs, int n_desc, int64_t n_items,
                                             int64_t b) {
-  if constexpr (NTH >= 256) {
-    static_assert(NTH % 256 == 0, "whole groups of four waves");
-    constexpr int G = traces_per_block(NTH);
+  constexpr int G = traces_per_block(NTH);
+  if constexpr (NTH % 256 == 0) {
     __shared__ double part[G][2][4];
     const int g = (int)threadIdx.x / 256;
     const int64_t item = b * G + g;
     trace_group<T, 2>(arena, descs, n_desc, item, item < n_items, (int)threadIdx.x % 256, part[g]);
   } else {
-    static_assert(NTH == 64, "one wave");
-    if (b < n_items) trace_wave<T, 2>(arena, descs, n_desc, b);
+    static_assert(NTH == 64 * G, "one trace per wave");
+    const int64_t item = b * G + (int)threadIdx.x / 64;
+    if (item < n_items) trace_wave<T, 2>(arena, descs, n_desc, item);
   }
 }
 
@@ -966,11 +949,16 @@ hec_bf16(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
   // [stage][plane][piece][row][k]: A rows are m, B rows are n (B is stored transposed)
   __shared__ __attribute__((aligned(16))) __bf16 As[ST][2][P][BM][PAD];
   __shared__ __attribute__((aligned(16))) __bf16 Bs[ST][2][P][BN][PAD];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  // ragged launches turn the waves' places as in hec_mfma
+  const int wave = __builtin_amdgcn_readfirstlane(FULL ? tid >> 6 : ((tid >> 6) + (int)blockIdx.x) % (NTH / 64));
   const int wm = wave / TL::WGN, wn = wave % TL::WGN, li = lane & 15, lk = lane >> 4;
 
   // loaded operands as whole register tuples (see Vec16)
   typedef float v2f __attribute__((ext_vector_type(2)));
+  // 16 (A) and 8 (B) bytes; at any element's address in a ragged launch
+  typedef typename Aligned<v4f, FULL>::V VA;
+  typedef typename Aligned<v2f, FULL>::V VB;
   v4f ra[LA][2];
   v2f rb[LB][8];
   auto gload = [&](const ItemView<float>& o, int k0) {
@@ -979,17 +967,14 @@ hec_bf16(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
       const int seg = tid + q * NTH;
       if (SEGA % NTH == 0 || seg < SEGA) {
         const int p = seg / (4 * BM), r = (seg % (4 * BM)) >> 2, qq = seg & 3;
-        const int am = o.m0 + r, ak = k0 + 8 * qq;
-        const float* src = o.A + (int64_t)p * o.M * o.K + (int64_t)am * o.K + ak;
-        if constexpr (FULL) {
-          ra[q][0] = reinterpret_cast<const v4f*>(src)[0];
-          ra[q][1] = reinterpret_cast<const v4f*>(src)[1];
-        } else {
-          float e[8];
-          const int av = am < o.M ? max(0, min(8, o.kend - ak)) : 0;
-          load8<float>(e, src, av, o.avec);
-#pragma unroll
-          for (int i = 0; i < 8; ++i) ra[q][i / 4][i % 4] = e[i];
+        // ragged: as in hec_mfma, unmasked loads at any alignment; rows past M
+        // load (and are split and multiplied) only up to the next 16
+        if (FULL || o.m0 + (r & ~15) < o.M) {
+          const int am = FULL ? o.m0 + r : min(o.m0 + r, o.M - 1);
+          const int ak = FULL || k0 + 8 * qq < o.kend ? k0 + 8 * qq : o.kbeg;
+          const float* src = o.A + ((int64_t)p * o.M + am) * o.K + ak;
+          ra[q][0] = reinterpret_cast<const VA*>(src)[0];
+          ra[q][1] = reinterpret_cast<const VA*>(src)[1];
         }
       }
     }
@@ -1000,27 +985,40 @@ hec_bf16(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
         const int p = seg / ((BK / 8) * (BN / 2)), rem = seg % ((BK / 8) * (BN / 2));
         const int g = rem / (BN / 2), cp = rem % (BN / 2);
         const int bk0 = k0 + 8 * g, bn = o.n0 + 2 * cp;
-        const float* src = o.B + (int64_t)p * o.K * o.N + (int64_t)bk0 * o.N + bn;
-        if (FULL || (bk0 + 8 <= o.kend && bn + 2 <= o.N && (o.N & 1) == 0)) {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) rb[q][i] = *reinterpret_cast<const v2f*>(src + (int64_t)i * o.N);
-        } else {
+        if (FULL || o.n0 + ((2 * cp) & ~15) < o.N) {
+          const float* src = o.B + (int64_t)p * o.K * o.N + (FULL || bn < o.N ? bn : o.n0);
 #pragma unroll
           for (int i = 0; i < 8; ++i)
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-              rb[q][i][c] = (bk0 + i < o.kend && bn + c < o.N) ? src[(int64_t)i * o.N + c] : 0.0f;
+            rb[q][i] = *reinterpret_cast<const VB*>(src + (int64_t)(FULL ? bk0 + i : min(bk0 + i, o.kend - 1)) * o.N);
         }
       }
     }
   };
-  auto sstore = [&](int st) {
+  // left: k elements of the loaded slice and those after it (as in hec_mfma)
+  auto sstore = [&](const ItemView<float>& o, int st, int left) {
     wait_loads();
+    if (!FULL && left < BK) {
+#pragma unroll
+      for (int q = 0; q < LA; ++q) {
+        const int k = 8 * ((tid + q * NTH) & 3);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (k + i >= left) ra[q][i / 4][i % 4] = 0.0f;
+      }
+#pragma unroll
+      for (int q = 0; q < LB; ++q) {
+        const int k = 8 * (((tid + q * NTH) % ((BK / 8) * (BN / 2))) / (BN / 2));
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (k + i >= left) rb[q][i] = v2f{0.0f, 0.0f};
+      }
+    }
 #pragma unroll
     for (int q = 0; q < LA; ++q) {
       const int seg = tid + q * NTH;
       if (SEGA % NTH == 0 || seg < SEGA) {
         const int p = seg / (4 * BM), r = (seg % (4 * BM)) >> 2, qq = seg & 3;
+        if (!FULL && o.m0 + (r & ~15) >= o.M) continue;
         // the 8 values as 4 adjacent pairs; each piece is one 16-byte row segment
         v2bf_t pc[4][P];
 #pragma unroll
@@ -1037,6 +1035,7 @@ hec_bf16(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
       if (SEGB % NTH == 0 || seg < SEGB) {
         const int p = seg / ((BK / 8) * (BN / 2)), rem = seg % ((BK / 8) * (BN / 2));
         const int g = rem / (BN / 2), cp = rem % (BN / 2);
+        if (!FULL && o.n0 + ((2 * cp) & ~15) >= o.N) continue;
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
           // column c's 8 values of k as 4 pairs of consecutive k
@@ -1076,19 +1075,24 @@ hec_bf16(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
 #pragma unroll
       for (int j = 0; j < TN; ++j) { cr[i][j] = v4f{0, 0, 0, 0}; ci[i][j] = v4f{0, 0, 0, 0}; }
 
-    // One k-slice of products from LDS stage st.
-    auto mma_slice = [&](int st) {
+    // the wave's blocks inside M x N
+    const int vi = FULL ? TM : max(0, min(TM, (cur.M - cur.m0 + 15) / 16 - wm * TM));
+    const int vj = FULL ? TN : max(0, min(TN, (cur.N - cur.n0 + 15) / 16 - wn * TN));
+    // One k-slice of products from LDS stage st, for the wave's first VI x VJ
+    // blocks.
+    auto mma_blocks = [&](auto vi_, auto vj_, int st) {
+      constexpr int VI = decltype(vi_)::value, VJ = decltype(vj_)::value;
       // one 16x16x32 step: lane holds k = 8*lk .. 8*lk+7 of row li (A) / column li (B)
-      v8bf a[TM][2][P], b[TN][2][P], bn[TN][P];   // [block][plane][piece]; bn: pieces of -Bi
+      v8bf a[VI][2][P], b[VJ][2][P], bn[VJ][P];   // [block][plane][piece]; bn: pieces of -Bi
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < VI; ++i)
 #pragma unroll
         for (int p = 0; p < 2; ++p)
 #pragma unroll
           for (int x = 0; x < P; ++x)
             a[i][p][x] = *reinterpret_cast<const v8bf*>(&As[st][p][x][(wm * TM + i) * 16 + li][8 * lk]);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
+      for (int j = 0; j < VJ; ++j) {
 #pragma unroll
         for (int p = 0; p < 2; ++p)
 #pragma unroll
@@ -1109,8 +1113,8 @@ hec_bf16(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
       // same order.
 #define MM(acc, u, v) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u, v, acc, 0, 0, 0)
 #define TERM(CR_X, CR_Y, CI_X, CI_Y)            \
-  _Pragma("unroll") for (int i = 0; i < TM; ++i) \
-  _Pragma("unroll") for (int j = 0; j < TN; ++j) { MM(cr[i][j], CR_X, CR_Y); MM(ci[i][j], CI_X, CI_Y); }
+  _Pragma("unroll") for (int i = 0; i < VI; ++i) \
+  _Pragma("unroll") for (int j = 0; j < VJ; ++j) { MM(cr[i][j], CR_X, CR_Y); MM(ci[i][j], CI_X, CI_Y); }
 #pragma unroll
       for (int t = 0; t < n_terms<P>(); ++t) {
         const int x = term_x<P>(t), y = term_y<P>(t);
@@ -1124,24 +1128,37 @@ hec_bf16(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
 #undef TERM
 #undef MM
     };
+    auto mma_slice = [&](int st) {
+      if constexpr (FULL) {
+        mma_blocks(Int<TM>{}, Int<TN>{}, st);
+      } else {
+        static_for<TM>([&](auto i_) {
+          static_for<TN>([&](auto j_) {
+            typedef Int<decltype(i_)::value + 1> VI;
+            typedef Int<decltype(j_)::value + 1> VJ;
+            if (vi == VI::value && vj == VJ::value) mma_blocks(VI{}, VJ{}, st);
+          });
+        });
+      }
+    };
     // The last slice is peeled off, as in hec_mfma: every pass of the loop
     // stores what it loaded.
-    const int nk = (cur.kend - cur.kbeg + BK - 1) / BK;
+    const int klen = cur.kend - cur.kbeg, nk = (klen + BK - 1) / BK;
     int c = 0;
     if (ST == 2) {
-      sstore(0);
+      sstore(cur, 0, klen);
       __syncthreads();
       for (; c + 1 < nk; ++c) {
         gload(cur, cur.kbeg + (c + 1) * BK);
         fence();
         mma_slice(c & 1);
         fence();
-        sstore((c & 1) ^ 1);
+        sstore(cur, (c & 1) ^ 1, klen - (c + 1) * BK);
         __syncthreads();
       }
     } else {
       for (; c + 1 < nk; ++c) {
-        sstore(0);
+        sstore(cur, 0, BK);
         __syncthreads();
         gload(cur, cur.kbeg + (c + 1) * BK);
         fence();
@@ -1149,7 +1166,7 @@ hec_bf16(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
         __syncthreads();
       }
       if (nk > 0) {
-        sstore(0);
+        sstore(cur, 0, klen - c * BK);
         __syncthreads();
       }
     }
@@ -1170,9 +1187,11 @@ hec_bf16(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TN; ++j) {
+        if (!FULL && (i >= vi || j >= vj)) continue;
         store_block<float, v4f, false, FULL>(C, M, N, cur.m0 + (wm * TM + i) * 16, cur.n0 + (wn * TN + j) * 16 + li,
                                              cr[i][j], ci[i][j], lk);
+      }
     if (!has_next) break;
     item = next;
     if (PF) {
@@ -1190,6 +1209,7 @@ static_assert(Tile2::BM == kTileShapes[2].bm && Tile2::BN == kTileShapes[2].bn &
 static_assert(Tile3::BM == kTileShapes[3].bm && Tile3::BN == kTileShapes[3].bn && Tile3::NTH == kTileShapes[3].nth, "tile 3");
 static_assert(Tile4::BM == kTileShapes[4].bm && Tile4::BN == kTileShapes[4].bn && Tile4::NTH == kTileShapes[4].nth, "tile 4");
 static_assert(Tile5::BM == kTileShapes[5].bm && Tile5::BN == kTileShapes[5].bn && Tile5::NTH == kTileShapes[5].nth, "tile 5");
+static_assert(Tile6::BM == kTileShapes[6].bm && Tile6::BN == kTileShapes[6].bn && Tile6::NTH == kTileShapes[6].nth, "tile 6");
 
 // Kernel of one launch variant in a per-precision table: K<TL, ST, PF, IN, TR>::fn()
 // is the kernel for tile TL, ST LDS stages, persistent grid PF, interior
@@ -1209,7 +1229,8 @@ const void* hec_pick(int stages, bool persistent, bool interior, bool traces) {
   return stages == 2 ? hec_pick_st<K, TL, 2>(persistent, interior, traces)
                      : hec_pick_st<K, TL, 1>(persistent, interior, traces);
 }
-template <template <class, int, bool, bool, bool> class K>
+// WIDE: the precision has kernels of tile 6.
+template <template <class, int, bool, bool, bool> class K, bool WIDE>
 const void* hec_table(int tile, int stages, bool persistent, bool interior, bool traces) {
   switch (tile) {
     case 0: return hec_pick<K, Tile0>(stages, persistent, interior, traces);
@@ -1218,6 +1239,13 @@ const void* hec_table(int tile, int stages, bool persistent, bool interior, bool
     case 3: return hec_pick<K, Tile3>(stages, persistent, interior, traces);
     case 4: return hec_pick<K, Tile4>(stages, persistent, interior, traces);
     case 5: return hec_pick<K, Tile5>(stages, persistent, interior, traces);
+    case 6:
+      if constexpr (WIDE) {
+        if (stages != 1 || persistent) return nullptr;
+        if (traces) return interior ? K<Tile6, 1, false, true, true>::fn() : K<Tile6, 1, false, false, true>::fn();
+        return interior ? K<Tile6, 1, false, true, false>::fn() : K<Tile6, 1, false, false, false>::fn();
+      }
+      return nullptr;
     default: return nullptr;
   }
 }

@@ -209,8 +209,7 @@ hipError_t launch(KernelCall& k, hipStream_t s) {
   return hipLaunchKernel(k.fn, dim3(k.grid), dim3(k.block), k.args, 0, s);
 }
 
-// variant = tile + kNumTiles * (grid + 2 * stage_choice), stage_choice 0: two
-// LDS stages, 1: one; grid 0: persistent, 1: one workgroup per work item.
+// variant: see desc.hpp (grid 0: persistent, 1: one workgroup per work item).
 // interior: every contraction of the launch passes hec_interior for the
 // variant's tile and the precision's k-step (the host checks it).
 hipError_t hec_call(int prec, int variant, bool interior, char* arena, int64_t desc_off, int n_desc, int64_t n_items,
@@ -224,10 +223,9 @@ hipError_t hec_call(int prec, int variant, bool interior, char* arena, int64_t d
     set_args(*k, arena, arena + desc_off, n_desc, n_items);
     return hipSuccess;
   }
-  if (variant < 0 || variant >= 4 * kNumTiles || prec < 0 || prec > 3) return hipErrorInvalidValue;
-  const int tile = variant % kNumTiles;
-  const bool persistent = (variant / kNumTiles) % 2 == 0;
-  const int stages = variant / (2 * kNumTiles) == 0 ? 2 : 1;
+  if (variant < 0 || variant >= kAllVariants || prec < 0 || prec > 3) return hipErrorInvalidValue;
+  const int tile = variant_tile(variant), stages = variant_stages(variant);
+  const bool persistent = variant_grid(variant) == 0;
   const void* fn = prec == 0   ? hec_kernel_f64(tile, stages, persistent, interior, traces)
                    : prec == 1 ? hec_kernel_f32(tile, stages, persistent, interior, traces)
                    : prec == 2 ? hec_kernel_bf16x2(tile, stages, persistent, interior, traces)

@@ -773,3 +773,25 @@ def test_index_pair_contractions_refused_in_split_bf16():
     with pytest.raises(X.CdagError) as e:
         run(wl, "tree", "bf16x3", True)
     assert e.value.code == B.E_INVALID
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3", "bf16x6"])
+@pytest.mark.parametrize("nvec,nt", [(17, 3), (33, 2), (45, 3), (80, 2), (97, 1)])
+def test_default_tiles(prec, nvec, nt):
+    """Without a choice every contraction runs the tile its GEMM calls for
+    (rings: K22; chains: K32 and K33, K33 in K splits): against the oracle, on N
+    with odd rows (loads at any alignment, a k tail, blocks outside), and the
+    same bits as the reported default tile chosen explicitly, which runs the
+    same products in the same order.  The error is norm-wise over the workload's
+    correlators: with one time slice a single trace may cancel to any size."""
+    kw = dict(nvec=nvec, nt=nt, sigma=1 / nvec ** 0.5, n_corr=2, seed=71)
+    for wl in (W.meson_ring(n_leaves=5, n_graphs=8, lmin=3, lmax=5, name="ring", **kw),
+               W.baryon_mix(n_bar=2, n_mes=3, n_graphs=3, name="chain", **{**kw, "sigma": 1 / nvec})):
+        ref = OV.correlators(wl)
+        tile = 2 if nvec % 48 == 0 else 1 if nvec % 32 == 0 or nvec < 32 else 0
+        a, b = run(wl, "tree", prec, True), run(wl, "tree", prec, True, tile=tile)
+        want, got = np.concatenate([ref[g] for g in ref]), np.concatenate([a["corr"][g] for g in ref])
+        err = np.linalg.norm(got - want) / np.linalg.norm(want)
+        print(f"{wl.name} N={nvec} {prec}: rel {err:.3e}")
+        assert err <= TOL[prec]
+        assert np.array_equal(np.concatenate(a["corr"]).view(np.uint64), np.concatenate(b["corr"]).view(np.uint64))

@@ -57,6 +57,23 @@ IndexMap index_map(const Spec& s, int n) {
   for (int j = 0; j < ro; ++j) at[s.perm[j]] = stride(ro, j);
   for (int d = 0; d < dm; ++d) m.c_m[d] = at[d];
   for (int d = 0; d < dn; ++d) m.c_n[d] = at[dm + d];
+  // The order of an index's digits is free (it only renumbers the GEMM's rows
+  // or columns): the output's unit-stride axis goes last in its index, so that a
+  // tile covers runs of it.  Where the operand's own unit-stride axis is
+  // another digit of that index, the larger of the two tensors decides (K
+  // elements of the operand against `other` of the output per row or column).
+  auto last_unit = [&](int nd, int64_t* oper, int64_t* out, int other) {
+    int to = -1, oo = -1;
+    for (int d = 0; d < nd; ++d) {
+      if (out[d] == 1) to = d;
+      if (oper[d] == 1) oo = d;
+    }
+    if (to < 0 || (oo >= 0 && oo != to && other < c)) return;
+    std::swap(oper[to], oper[nd - 1]);
+    std::swap(out[to], out[nd - 1]);
+  };
+  last_unit(dm, m.a_m, m.c_m, dn);
+  last_unit(dn, m.b_n, m.c_n, dm);
   return m;
 }
 

@@ -157,20 +157,6 @@ struct ItemView {
   const IndexMap* map;   // a contraction over any index pairs, else nullptr
 };
 
-// Element offset of a mixed-radix index x (nd digits in radix n, most
-// significant first) with per-digit strides st.
-__device__ __forceinline__ int64_t digit_offset(int64_t x, int nd, int n, const int64_t* st) {
-  int64_t off = 0;
-#pragma unroll
-  for (int d = 2; d >= 0; --d) {
-    if (d < nd) {
-      off += (x % n) * st[d];
-      x /= n;
-    }
-  }
-  return off;
-}
-
 template <typename T, int BM, int BN>
 __device__ __forceinline__ ItemView<T> view_item(char* arena, const HecDesc* descs, int n_desc, int64_t item) {
   const WorkItem w = decode_item<BM, BN>(descs, n_desc, item);
@@ -462,14 +448,12 @@ __device__ __forceinline__ void trace_block(char* arena, const HcaDesc* descs, i
 // displacing the operands that its other work items are still reading from L2.
 template <typename T, typename V, bool NT, bool INNER = false>
 __device__ __forceinline__ void store_block(T* C, int M, int N, int row0, int col, const V& re, const V& im,
-                                           int lk, const IndexMap* map = nullptr) {
+                                           int lk) {
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int m = row0 + Mfma<T>::row(lk, v);
     if (INNER || (m < M && col < N)) {
-      // a general contraction writes C(m, n) at its output axis order
-      const int64_t off = map ? digit_offset(m, map->dm, map->n, map->c_m) + digit_offset(col, map->dn, map->n, map->c_n)
-                              : (int64_t)m * N + col;
+      const int64_t off = (int64_t)m * N + col;
       T* pr = &C[off];
       T* pi = &C[(int64_t)M * N + off];
       if (NT) {
@@ -487,20 +471,17 @@ __device__ __forceinline__ void store_block(T* C, int M, int N, int row0, int co
 // buffer refilled from the register prefetch (two barriers per k-chunk, half
 // the LDS, more workgroups per compute unit).  PF: a workgroup that strides
 // over several items (persistent grid) prefetches its next item.
-// GEN: every work item is a contraction over any index pairs; operands are
-// loaded and the output stored through its IndexMap, element by element.
 // FULL: every contraction of the launch is interior (hec_interior): operands
 // load with unpredicated 16-byte loads and outputs store without bounds tests.
 // TR: the launch also carries the root traces of its plan step (n_titems
 // (root, t) items described by tdescs), in the workgroups after the
 // contractions' work items (one workgroup per item; trace_block); without TR
 // the last three arguments are unused.
-template <typename T, class TL, int ST, bool PF, bool GEN = false, bool FULL = false, bool TR = false>
-__global__ void __launch_bounds__(TL::NTH, (occupancy_waves<sizeof(T) == 8 ? 0 : 1, TL, ST, PF, !FULL && !GEN>()))
+template <typename T, class TL, int ST, bool PF, bool FULL = false, bool TR = false>
+__global__ void __launch_bounds__(TL::NTH, (occupancy_waves<sizeof(T) == 8 ? 0 : 1, TL, ST, PF, !FULL>()))
 hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc, int64_t n_items,
          const HcaDesc* __restrict__ tdescs, int n_tdesc, int64_t n_titems) {
-  static_assert(!(GEN && FULL), "a general contraction is never interior");
-  static_assert(!(TR && (PF || GEN)), "traces ride only in launches of one workgroup per item");
+  static_assert(!(TR && PF), "traces ride only in launches of one workgroup per item");
   typedef typename Mfma<T>::V V;
   constexpr int NTH = TL::NTH, BM = TL::BM, BN = TL::BN, TM = TL::TM, TN = TL::TN;
   // k-slice: 16 (FP64) or 32 (FP32) k per LDS stage, so that a K = 64
@@ -533,7 +514,7 @@ hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
   // M x N and the 4-deep k steps past the k range; the waves' places in the
   // tile turn with the workgroup, so that the places with fewer blocks fall on
   // every SIMD alike.
-  constexpr bool RAG = !FULL && !GEN;
+  constexpr bool RAG = !FULL;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(RAG ? ((tid >> 6) + (int)blockIdx.x) % (NTH / 64) : tid >> 6);
   const int wm = wave / TL::WGN, wn = wave % TL::WGN, li = lane & 15, lk = lane >> 4;
@@ -568,55 +549,26 @@ hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
       }
       return;
     }
-    if constexpr (!GEN) {
-      // Ragged: the same 16-byte loads at any alignment, with no mask.  Rows
-      // past M repeat row M - 1 and columns past N take what follows the row:
-      // their products reach only outputs that are not stored.  Elements past
-      // the k range are zeroed on their way to LDS (sstore).  A segment that
-      // starts past a row's or the k range's end loads the range's start
-      // instead, so a load ends at most 7 elements (56 bytes) past its tensor,
-      // which the arena always holds (descriptor tables and results follow
-      // every tensor).  Element-wise loads behind one test each were the bound
-      // before: FP64 K22 at N = 45 18 -> 21 TFLOP/s and FP32 at N = 48 25 -> 33
-      // on the default tiles (66 on the one-stage 64 x 64 one), FP64 C1..C3 at
-      // N = 24 20 -> 25, bits unchanged.
-#pragma unroll
-      for (int q = 0; q < LA; ++q) {
-        const int seg = tid + q * NTH;
-        if (SEGA % NTH == 0 || seg < SEGA) {
-          const int p = seg / (SPR * BM), r = (seg % (SPR * BM)) / SPR, hh = seg % SPR;
-          const int am = min(o.m0 + r, o.M - 1), ak = k0 + 8 * hh < o.kend ? k0 + 8 * hh : o.kbeg;
-          const T* src = o.A + ((int64_t)p * o.M + am) * o.K + ak;
-#pragma unroll
-          for (int j = 0; j < NA; ++j) ra[q][j] = *reinterpret_cast<const VU*>(src + W * j);
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < LB; ++q) {
-        const int seg = tid + q * NTH;
-        if (SEGB % NTH == 0 || seg < SEGB) {
-          const int p = seg / (BK * (BN / W)), rem = seg % (BK * (BN / W));
-          const int kk = rem / (BN / W), cw = rem % (BN / W);
-          const int bk = min(k0 + kk, o.kend - 1), bn = o.n0 + W * cw < o.N ? o.n0 + W * cw : o.n0;
-          rb[q] = *reinterpret_cast<const VU*>(o.B + ((int64_t)p * o.K + bk) * o.N + bn);
-        }
-      }
-      return;
-    }
-    // general: element by element through the index map
+    // Ragged: the same 16-byte loads at any alignment, with no mask.  Rows
+    // past M repeat row M - 1 and columns past N take what follows the row:
+    // their products reach only outputs that are not stored.  Elements past
+    // the k range are zeroed on their way to LDS (sstore).  A segment that
+    // starts past a row's or the k range's end loads the range's start
+    // instead, so a load ends at most 7 elements (56 bytes) past its tensor,
+    // which the arena always holds (descriptor tables and results follow
+    // every tensor).  Element-wise loads behind one test each were the bound
+    // before: FP64 K22 at N = 45 18 -> 21 TFLOP/s and FP32 at N = 48 25 -> 33
+    // on the default tiles (66 on the one-stage 64 x 64 one), FP64 C1..C3 at
+    // N = 24 20 -> 25, bits unchanged.
 #pragma unroll
     for (int q = 0; q < LA; ++q) {
       const int seg = tid + q * NTH;
       if (SEGA % NTH == 0 || seg < SEGA) {
         const int p = seg / (SPR * BM), r = (seg % (SPR * BM)) / SPR, hh = seg % SPR;
-        const int am = o.m0 + r, ak = k0 + 8 * hh;
-        const IndexMap& mp = *o.map;
-        const T* plane = o.A + (int64_t)p * o.M * o.K;
-        const int64_t row = am < o.M ? digit_offset(am, mp.dm, mp.n, mp.a_m) : 0;
+        const int am = min(o.m0 + r, o.M - 1), ak = k0 + 8 * hh < o.kend ? k0 + 8 * hh : o.kbeg;
+        const T* src = o.A + ((int64_t)p * o.M + am) * o.K + ak;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-          ra[q][i / W][i % W] =
-              (am < o.M && ak + i < o.kend) ? plane[row + digit_offset(ak + i, mp.dk, mp.n, mp.a_k)] : T(0);
+        for (int j = 0; j < NA; ++j) ra[q][j] = *reinterpret_cast<const VU*>(src + W * j);
       }
     }
 #pragma unroll
@@ -625,13 +577,8 @@ hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
       if (SEGB % NTH == 0 || seg < SEGB) {
         const int p = seg / (BK * (BN / W)), rem = seg % (BK * (BN / W));
         const int kk = rem / (BN / W), cw = rem % (BN / W);
-        const int bkk = k0 + kk, bn = o.n0 + W * cw;
-        const IndexMap& mp = *o.map;
-        const T* plane = o.B + (int64_t)p * o.K * o.N;
-        const int64_t row = bkk < o.kend ? digit_offset(bkk, mp.dk, mp.n, mp.b_k) : 0;
-#pragma unroll
-        for (int i = 0; i < W; ++i)
-          rb[q][i] = (bkk < o.kend && bn + i < o.N) ? plane[row + digit_offset(bn + i, mp.dn, mp.n, mp.b_n)] : T(0);
+        const int bk = min(k0 + kk, o.kend - 1), bn = o.n0 + W * cw < o.N ? o.n0 + W * cw : o.n0;
+        rb[q] = *reinterpret_cast<const VU*>(o.B + ((int64_t)p * o.K + bk) * o.N + bn);
       }
     }
   };
@@ -851,7 +798,7 @@ hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc
           }
         } else {
           store_block<T, V, true, FULL>(C, M, N, cur.m0 + (wm * TM + i) * 16, cur.n0 + (wn * TN + j) * 16 + li,
-                                        re, im, lk, GEN ? cur.map : nullptr);
+                                        re, im, lk);
         }
       }
     if constexpr (CT) {

@@ -1,14 +1,14 @@
 // Kernel table of the exterior contractions in FP64: every tile, LDS
 // stage count, grid policy, interior flag and carried traces. Also the general kernel
 // (contractions over any index pairs).
-#include "hec.hpp"
+#include "hec_gen.hpp"
 #include "kernels.hpp"
 
 namespace cdag {
 namespace {
 template <class TL, int ST, bool PF, bool IN, bool TR>
 struct Kern {
-  static const void* fn() { return reinterpret_cast<const void*>(&hec_mfma<double, TL, ST, PF, false, IN, TR>); }
+  static const void* fn() { return reinterpret_cast<const void*>(&hec_mfma<double, TL, ST, PF, IN, TR>); }
 };
 }  // namespace
 
@@ -17,7 +17,7 @@ const void* hec_kernel_f64(int tile, int stages, bool persistent, bool interior,
 }
 
 const void* hec_general_f64() {
-  return reinterpret_cast<const void*>(&hec_mfma<double, Tile1, 2, false, true, false>);
+  return reinterpret_cast<const void*>(&hec_general<double>);
 }
 
 }  // namespace cdag

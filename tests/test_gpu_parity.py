@@ -795,3 +795,19 @@ def test_default_tiles(prec, nvec, nt):
         print(f"{wl.name} N={nvec} {prec}: rel {err:.3e}")
         assert err <= TOL[prec]
         assert np.array_equal(np.concatenate(a["corr"]).view(np.uint64), np.concatenate(b["corr"]).view(np.uint64))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nvec,nt", [(5, 2), (16, 2), (17, 3), (24, 1)])
+def test_general_kernel_sizes(prec, nvec, nt):
+    """Contractions over any index pairs at the edges of the general kernel:
+    fewer rows than a tile, K a whole number of its 256-entry offset tables
+    (N = 16, two pairs), one past it (17) and several (24), against the
+    oracle."""
+    wl = W.pairs_mix(nvec=nvec, nt=nt, n_graphs=14, seed=72)
+    ref = OV.correlators(wl)
+    a = run(wl, "tree", prec, True)
+    want, got = np.concatenate([ref[g] for g in ref]), np.concatenate([a["corr"][g] for g in ref])
+    err = np.linalg.norm(got - want) / np.linalg.norm(want)
+    print(f"pairs N={nvec} {prec}: rel {err:.3e}")
+    assert err <= TOL[prec]

@@ -143,6 +143,47 @@ __global__ void __launch_bounds__(256) to_planar(const S* __restrict__ src, T* _
   }
 }
 
+// ------------------------------------------------------------------ host transfers
+// The uploads, or the spills, of one plan step in one launch: workgroup b moves
+// the chunk (mb.chunk bytes) that it holds of its move, between device memory
+// and pinned host memory, every load of a thread ahead of its first store.
+//
+// A replayed graph runs its copies one after another, as copy kernels of 5 to 6
+// us each for small tensors (16 leaf slices of 128 KiB: 100 us a pass); one
+// launch keeps every tensor's reads in flight on the link at once (15 slices in
+// 37 us, 53 GB/s).  Chunks of one load per thread for a small batch, which
+// spreads it over more compute units (4 tensors of 32 KiB 8.6 -> 4.7 us), of four
+// for a large one (the 15 slices above take 43 us in small chunks).
+template <int Q>
+__device__ __forceinline__ void move_chunk(const char* src, char* dst, int64_t left) {
+  typedef double v2d __attribute__((ext_vector_type(2)));
+  const int tid = threadIdx.x;
+  v2d r[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+    if (16 * (tid + 256 * q) < left) r[q] = reinterpret_cast<const v2d*>(src)[tid + 256 * q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+    if (16 * (tid + 256 * q) < left) reinterpret_cast<v2d*>(dst)[tid + 256 * q] = r[q];
+}
+
+__global__ void __launch_bounds__(256) move_kernel(const MoveBatch mb) {
+  int i = 0;
+  while (i + 1 < mb.n && mb.begin[i + 1] <= (int)blockIdx.x) ++i;
+  const Move m = mb.move[i];
+  const int64_t off = (int64_t)((int)blockIdx.x - mb.begin[i]) * mb.chunk;
+  const int64_t left = m.bytes - off < mb.chunk ? m.bytes - off : mb.chunk;
+  const char* src = static_cast<const char*>(m.src) + off;
+  char* dst = static_cast<char*>(m.dst) + off;
+  if ((((uintptr_t)src | (uintptr_t)dst | (uint64_t)left) & 15) == 0) {
+    if (mb.chunk <= kMoveChunk) move_chunk<1>(src, dst, left);
+    else move_chunk<4>(src, dst, left);
+  } else {   // slices of odd length: whole complex64 values (8 bytes)
+    for (int64_t e = threadIdx.x; e < left / 8; e += 256)
+      reinterpret_cast<double*>(dst)[e] = reinterpret_cast<const double*>(src)[e];
+  }
+}
+
 // ------------------------------------------------------------------ launchers
 namespace {
 // Persistent launches: at most as many workgroups as can be resident at once
@@ -306,6 +347,40 @@ hipError_t launch_hca(int prec, char* arena, int64_t desc_off, int n_desc, int64
   KernelCall k;
   const hipError_t e = hca_call(prec, arena, desc_off, n_desc, n_items, &k);
   return e != hipSuccess ? e : launch(k, s);
+}
+
+int make_moves(const Move* moves, int n, MoveBatch* mb) {
+  int64_t bytes = 0, chunks = 0;
+  for (int i = 0; i < n && i < kMaxMoves; ++i) bytes += moves[i].bytes;
+  mb->chunk = bytes <= kMoveSmall ? kMoveChunk : 4 * kMoveChunk;
+  mb->n = 0;
+  while (mb->n < n && mb->n < kMaxMoves) {
+    const int64_t more = (moves[mb->n].bytes + mb->chunk - 1) / mb->chunk;
+    if (mb->n > 0 && chunks + more > kMaxGrid) break;
+    if (chunks + more > INT32_MAX / 256) return -1;
+    mb->move[mb->n] = moves[mb->n];
+    mb->begin[mb->n++] = (int32_t)chunks;
+    chunks += more;
+  }
+  mb->begin[mb->n] = (int32_t)chunks;
+  return mb->n;
+}
+
+const void* move_fn() { return reinterpret_cast<const void*>(&move_kernel); }
+
+hipError_t launch_moves(const Move* moves, int n, hipStream_t s) {
+  for (int done = 0; done < n;) {
+    MoveBatch mb;
+    const int k = make_moves(moves + done, n - done, &mb);
+    if (k <= 0) return hipErrorInvalidValue;
+    void* args[1] = {&mb};
+    if (mb.begin[k] > 0) {
+      const hipError_t e = hipLaunchKernel(move_fn(), dim3((unsigned)mb.begin[k]), dim3(256), args, 0, s);
+      if (e != hipSuccess) return e;
+    }
+    done += k;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_to_planar(bool src_double, bool dst_double, const void* src, void* dst, int64_t nt, int64_t e,

@@ -66,6 +66,26 @@ const void* hec_kernel_bf16x2(int tile, int stages, bool persistent, bool interi
 const void* hec_kernel_bf16x3(int tile, int stages, bool persistent, bool interior, bool traces);
 const void* hec_general_f64();
 const void* hec_general_f32();
+// Transfers between device memory and pinned host memory by a kernel, up to
+// kMaxMoves in one launch (passed by value, so that a captured launch holds
+// them).  Bytes, and both addresses, are multiples of 8.
+constexpr int kMaxMoves = 32;
+constexpr int kMoveChunk = 4096;           // bytes per workgroup, four times that for a batch
+constexpr int64_t kMoveSmall = 512 << 10;  // of more bytes than this
+struct Move {
+  const void* src;
+  void* dst;
+  int64_t bytes;
+};
+struct MoveBatch {
+  int32_t n, chunk;
+  int32_t begin[kMaxMoves + 1];   // first chunk of each move; begin[n]: all chunks (the grid)
+  Move move[kMaxMoves];
+};
+// Takes moves[0 .. k) into one batch and returns k (-1: a move too large).
+int make_moves(const Move* moves, int n, MoveBatch* mb);
+const void* move_fn();
+hipError_t launch_moves(const Move* moves, int n, hipStream_t s);
 // Interleaved complex [nt][e] (double or float) -> device layout [nt][2][e]
 // (double or float), both in device memory.
 hipError_t launch_to_planar(bool src_double, bool dst_double, const void* src, void* dst, int64_t nt, int64_t e,

@@ -56,6 +56,9 @@ double now() {
 
 // Stream roles; trace records and event ids use these numbers.
 enum StreamRole : int { S_COMP = 0, S_H2D = 1, S_D2H = 2, kStreams = 3 };
+// Most bytes of a step's transfers, in one direction, that eager issue moves by
+// a kernel.
+constexpr int64_t kEagerMoveBytes = 8 << 20;
 }  // namespace
 
 // ---------------------------------------------------------------- static scratch
@@ -441,6 +444,17 @@ int64_t walk_steps(const Ctx& c, int64_t g0, int64_t g1, bool one_stream, bool i
   return n_launch;
 }
 
+// Ends of one transfer of pass m: an upload from the leaf's staging or the
+// spill pool, or a spill.
+Move move_of(const Ctx& c, const Device& D, int prec, const PlanRec& r, const PassMap& m) {
+  char* spill = (char*)D.spill;
+  char* dev = D.arena + m.dev(r.dev_off);
+  if (r.op == OP_D2H) return {dev, spill + m.host(r.host_off), m.bytes(r.node)};
+  const void* src = c.dag.is_leaf(r.node) ? (const void*)((const char*)D.stage[prec][r.node] + m.stage(r.node))
+                                          : (const void*)(spill + m.host(r.host_off));
+  return {src, dev, m.bytes(r.node)};
+}
+
 // The issuing form: kernels on st[S_COMP], uploads on st[S_H2D], spills on
 // st[S_D2H], with the device's per-step and per-pass events.
 struct HipOps {
@@ -450,42 +464,80 @@ struct HipOps {
   hipStream_t st[kStreams];
   Device* timed;
 
+  std::vector<Move> moves[kStreams]{};   // of the step, not yet issued
+
   void wait(int to, int from, int64_t g, int64_t) { HIPC(hipStreamWaitEvent(st[to], D.ev[from][g], 0)); }
-  void record(int r, int64_t g) { HIPC(hipEventRecord(D.ev[r][g], st[r])); }
+  void record(int r, int64_t g) {   // comes after the step's transfers on r
+    flush(r);
+    HIPC(hipEventRecord(D.ev[r][g], st[r]));
+  }
   void wait_pass(int to, int from, int64_t k, int64_t) { HIPC(hipStreamWaitEvent(st[to], D.ev_end[from][k], 0)); }
   void record_pass(int r, int64_t k, int64_t) { HIPC(hipEventRecord(D.ev_end[r][k], st[r])); }
   int64_t launch(int64_t g, const PassMap&) { return launch_step(c.kplan, g, prec, D.arena, st[S_COMP], timed); }
-  void transfer(const PlanRec& r, const PassMap& m, int64_t g) {
-    const size_t sz = (size_t)m.bytes(r.node);
-    hipStream_t cs = st[r.op == OP_D2H ? S_D2H : S_H2D];
-    hipEvent_t ta = nullptr, tb = nullptr;
-    if (timed) {
-      ta = timed->timing_event();
-      tb = timed->timing_event();
-      HIPC(hipEventRecord(ta, cs));
-    }
-    char* spill = (char*)D.spill;
-    if (r.op == OP_D2H) {
-      HIPC(hipMemcpyAsync(spill + m.host(r.host_off), D.arena + m.dev(r.dev_off), sz, hipMemcpyDeviceToHost, cs));
+  void copy(int r, const Move& mv) {
+    HIPC(hipMemcpyAsync(mv.dst, mv.src, (size_t)mv.bytes, r == S_D2H ? hipMemcpyDeviceToHost : hipMemcpyHostToDevice,
+                        st[r]));
+  }
+  // Small transfers of a step go in one launch (a copy costs 5 to 10 us of its
+  // own on a stream: a pass with 4 leaves of 32 KiB 113 -> 86 us, one with 12 of
+  // 680 KB 1.13 -> 1.00 ms); large ones to the copy engines, which leave the
+  // compute units to the kernels (leaves of 17 MB a pass).
+  void flush(int r) {
+    int64_t bytes = 0;
+    for (const Move& mv : moves[r]) bytes += mv.bytes;
+    if (bytes <= kEagerMoveBytes && !(D.spill_pageable && D.spill)) {
+      HIPC(launch_moves(moves[r].data(), (int)moves[r].size(), st[r]));
     } else {
-      const void* src = c.dag.is_leaf(r.node) ? (const void*)((const char*)D.stage[prec][r.node] + m.stage(r.node))
-                                              : (const void*)(spill + m.host(r.host_off));
-      HIPC(hipMemcpyAsync(D.arena + m.dev(r.dev_off), src, sz, hipMemcpyHostToDevice, cs));
+      for (const Move& mv : moves[r]) copy(r, mv);
     }
-    if (timed) {
-      HIPC(hipEventRecord(tb, cs));
-      const int32_t kd = c.dag.kind[r.node];
-      timed->tpairs.push_back({-2, r.op == OP_D2H ? CDAG_LAUNCH_D2H : CDAG_LAUNCH_H2D,
-                               kd >= 0 ? (1 << kd) : 0, g, (double)sz, ta, tb});
+    moves[r].clear();
+  }
+  void transfer(const PlanRec& r, const PassMap& m, int64_t g) {
+    const Move mv = move_of(c, D, prec, r, m);
+    const int role = r.op == OP_D2H ? S_D2H : S_H2D;
+    if (!timed) {
+      moves[role].push_back(mv);
+      return;
     }
+    hipEvent_t ta = timed->timing_event(), tb = timed->timing_event();
+    HIPC(hipEventRecord(ta, st[role]));
+    copy(role, mv);
+    HIPC(hipEventRecord(tb, st[role]));
+    const int32_t kd = c.dag.kind[r.node];
+    timed->tpairs.push_back({-2, r.op == OP_D2H ? CDAG_LAUNCH_D2H : CDAG_LAUNCH_H2D,
+                             kd >= 0 ? (1 << kd) : 0, g, (double)mv.bytes, ta, tb});
   }
 };
 
-int64_t issue_steps(Ctx& c, Device& D, int prec, int64_t g0, int64_t g1, hipStream_t comp, hipStream_t h2d,
-                    hipStream_t d2h, Device* timed, bool in_capture) {
-  HipOps ops{c, D, prec, {comp, h2d, d2h}, timed};
-  return walk_steps(c, g0, g1, comp == h2d, in_capture, ops);
-}
+// The one-stream form that segments are captured with: stream order carries
+// every dependency, and the spills, then the uploads, of a step are one launch
+// each.
+struct SegmentOps {
+  const Ctx& c;
+  Device& D;
+  int prec;
+  hipStream_t st;
+  std::vector<Move> moves{};
+  int32_t dir = OP_D2H;
+
+  void wait(int, int, int64_t, int64_t) {}
+  void record(int, int64_t) {}
+  void wait_pass(int, int, int64_t, int64_t) {}
+  void record_pass(int, int64_t, int64_t) {}
+  void flush() {
+    if (!moves.empty()) HIPC(launch_moves(moves.data(), (int)moves.size(), st));
+    moves.clear();
+  }
+  void transfer(const PlanRec& r, const PassMap& m, int64_t) {
+    if (r.op != dir) flush();
+    dir = r.op;
+    moves.push_back(move_of(c, D, prec, r, m));
+  }
+  int64_t launch(int64_t g, const PassMap&) {
+    flush();
+    return launch_step(c.kplan, g, prec, D.arena, st, nullptr);
+  }
+};
 
 // The recording form: the same walk with no HIP call, writing what each stream
 // would do (event records and waits, and the byte ranges that every transfer
@@ -577,6 +629,7 @@ struct GraphOps {
   std::vector<hipGraphNode_t> ev_node[kStreams];     // per global step
   std::vector<hipGraphNode_t> pass_node[kStreams];   // per pass
   std::vector<hipGraphNode_t> deps;
+  std::vector<Move> moves[kStreams];                 // of the step, not yet added
 
   GraphOps(const Ctx& ctx, Device& dev, int p, hipGraph_t g) : c(ctx), D(dev), prec(p), graph(g) {
     const size_t G = (size_t)(ctx.plan.chunks() * (int64_t)ctx.plan.steps.size());
@@ -604,46 +657,45 @@ struct GraphOps {
   void wait(int to, int from, int64_t g, int64_t) {
     if (ev_node[from][g]) pending[to].push_back(ev_node[from][g]);
   }
-  void record(int r, int64_t g) { ev_node[r][g] = head(r); }
+  void record(int r, int64_t g) {   // comes after the step's transfers on r
+    flush(r);
+    ev_node[r][g] = head(r);
+  }
   void wait_pass(int to, int from, int64_t k, int64_t) {
     if (pass_node[from][k]) pending[to].push_back(pass_node[from][k]);
   }
   void record_pass(int r, int64_t k, int64_t) { pass_node[r][k] = head(r); }
   void transfer(const PlanRec& r, const PassMap& m, int64_t) {
-    const size_t sz = (size_t)m.bytes(r.node);
-    const int sr = r.op == OP_D2H ? S_D2H : S_H2D;
-    char* spill = (char*)D.spill;
-    void* dst;
-    const void* src;
-    hipMemcpyKind kind;
-    if (r.op == OP_D2H) {
-      dst = spill + m.host(r.host_off);
-      src = D.arena + m.dev(r.dev_off);
-      kind = hipMemcpyDeviceToHost;
-    } else {
-      dst = D.arena + m.dev(r.dev_off);
-      src = c.dag.is_leaf(r.node) ? (const void*)((const char*)D.stage[prec][r.node] + m.stage(r.node))
-                                  : (const void*)(spill + m.host(r.host_off));
-      kind = hipMemcpyHostToDevice;
+    moves[r.op == OP_D2H ? S_D2H : S_H2D].push_back(move_of(c, D, prec, r, m));
+  }
+  // one node per kMaxMoves of the step's transfers of stream r
+  void flush(int r) {
+    for (size_t done = 0; done < moves[r].size();) {
+      MoveBatch mb;
+      const int k = make_moves(moves[r].data() + done, (int)(moves[r].size() - done), &mb);
+      if (k <= 0) throw Error(CDAG_E_INVALID, "transfer too large");
+      void* args[1] = {&mb};
+      if (mb.begin[k] > 0) add_kernel(r, move_fn(), (unsigned)mb.begin[k], 256, args);
+      done += (size_t)k;
     }
-    deps_of(sr);
+    moves[r].clear();
+  }
+  void add_kernel(int r, const void* fn, unsigned grid, unsigned block, void** args) {
+    hipKernelNodeParams np{};
+    np.func = const_cast<void*>(fn);
+    np.gridDim = dim3(grid);
+    np.blockDim = dim3(block);
+    np.sharedMemBytes = 0;
+    np.kernelParams = args;
+    np.extra = nullptr;
+    deps_of(r);
     hipGraphNode_t n = nullptr;
-    HIPC(hipGraphAddMemcpyNode1D(&n, graph, deps.data(), deps.size(), dst, src, sz, kind));
-    added(sr, n);
+    HIPC(hipGraphAddKernelNode(&n, graph, deps.data(), deps.size(), &np));
+    added(r, n);
   }
   void kernel(KernelCall& k) {
     k.bind();
-    hipKernelNodeParams np{};
-    np.func = const_cast<void*>(k.fn);
-    np.gridDim = dim3(k.grid);
-    np.blockDim = dim3(k.block);
-    np.sharedMemBytes = 0;
-    np.kernelParams = k.args;
-    np.extra = nullptr;
-    deps_of(S_COMP);
-    hipGraphNode_t n = nullptr;
-    HIPC(hipGraphAddKernelNode(&n, graph, deps.data(), deps.size(), &np));
-    added(S_COMP, n);
+    add_kernel(S_COMP, k.fn, k.grid, k.block, k.args);
   }
   int64_t launch(int64_t g, const PassMap&) {
     const KernelPlan& kp = c.kplan;
@@ -858,7 +910,8 @@ hipGraph_t capture_steps(Ctx& c, Device& D, int prec, int64_t g0, int64_t g1, bo
   hipGraph_t g = nullptr;
   HIPC(hipStreamBeginCapture(D.cap, hipStreamCaptureModeThreadLocal));
   try {
-    issue_steps(c, D, prec, g0, g1, D.cap, D.cap, D.cap, nullptr, true);
+    SegmentOps ops{c, D, prec, D.cap};
+    walk_steps(c, g0, g1, true, true, ops);
     if (last) HIPC(launch_finish(c.kplan, D.arena, (char*)D.results, D.cap));
   } catch (...) {
     ignore(hipStreamEndCapture(D.cap, &g));
@@ -971,7 +1024,8 @@ void device_execute(Ctx& c, int prec, int batched, cdag_exec_stats* st) {
     n_segments = (int64_t)D.seg_exec.size();
     for (int64_t g = 0; g < G; ++g) n_launch += kp.launch_off[g + 1] - kp.launch_off[g];
   } else {
-    n_launch += issue_steps(c, D, prec, 0, G, D.comp, D.copy, D.spill_s, timed, false);
+    HipOps ops{c, D, prec, {D.comp, D.copy, D.spill_s}, timed, {}};
+    n_launch += walk_steps(c, 0, G, false, false, ops);
     // the results copy and the caller's later work follow every transfer
     HIPC(hipEventRecord(D.ev_join[0], D.copy));
     HIPC(hipEventRecord(D.ev_join[1], D.spill_s));

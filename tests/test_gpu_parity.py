@@ -811,3 +811,33 @@ def test_general_kernel_sizes(prec, nvec, nt):
     err = np.linalg.norm(got - want) / np.linalg.norm(want)
     print(f"pairs N={nvec} {prec}: rel {err:.3e}")
     assert err <= TOL[prec]
+
+
+@pytest.mark.parametrize("nvec,nt,chunks,n_leaves", [(3, 1, 1, 40), (9, 6, 3, 6), (64, 4, 2, 6), (24, 8, 1, 34)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_grouped_transfers(prec, nvec, nt, chunks, n_leaves):
+    """A step's uploads and spills in one launch (more tensors than one launch
+    holds, slices that are no whole 16 bytes, chunks of both sizes) give the
+    bits of resident leaves in every issue mode, replays included, under a
+    budget that spills."""
+    import paper_2511_02257_amd as X
+    from paper_2511_02257_amd.device import DeviceRunner
+    wl = W.meson_ring(n_leaves=n_leaves, nvec=nvec, nt=nt, n_graphs=40, lmin=4, lmax=6, sigma=nvec ** -0.5, n_corr=2,
+                      seed=73)
+    ctx = X.Context()
+    ctx.build_cdag(wl.leaves, wl.graphs)
+    _, _, peak = ctx.memsim(ctx.schedule("input"), 16 if prec == "fp64" else 8)
+    ctx.schedule("tree")
+    runner = DeviceRunner(ctx, 0)
+    ctx.set_options(leaves_resident=True, wave_lookahead=16)
+    runner.run(prec, True)
+    want = np.concatenate(ctx.fetch_correlators()).view(np.uint64).copy()
+    ctx.set_time_chunks(chunks)
+    for budget in (None, peak // 3):
+        ctx.set_mem_budget(budget)
+        for mode in (0, 1, 2):
+            ctx.set_options(leaves_resident=False, wave_lookahead=16, use_graphs=mode)
+            for _ in range(3):
+                runner.run(prec, True)
+                assert np.array_equal(np.concatenate(ctx.fetch_correlators()).view(np.uint64), want), (budget, mode)
+    ctx.close()

@@ -185,7 +185,8 @@ typedef struct {
   int32_t interior;   /* HEC: 1 when every contraction of the launch is a whole number of
                          tiles and k-steps with aligned rows, so the kernel ran its
                          form without bounds tests; else 0                              */
-  int64_t step;       /* plan step (wave); -1 for the cross-diagram sum                */
+  int64_t step;       /* execution step (one or more plan steps issued together);
+                         -1 for the cross-diagram sum                                   */
   int64_t n_items;    /* workgroup work items; H2D, D2H: 1                               */
   double flops;       /* algorithmic flops (8 per complex multiply-add); transfers: 0   */
   double bytes;       /* HEC, HCA: algorithmic bytes (each distinct operand of the launch
@@ -209,11 +210,13 @@ typedef struct {
   int32_t stream;   /* 0: the compute stream, 1: the upload stream, 2: the spill stream  */
   int64_t seq;      /* READ, WRITE: number of the operation (one host transfer, or all
                        kernels of one step) they belong to; -1 for events               */
-  int64_t step;     /* plan step that issues the record                                  */
+  int64_t step;     /* execution step that issues the record; READ and WRITE of a
+                       transfer: the plan step                                            */
   int64_t node;     /* READ, WRITE: the tensor; -1 for events                            */
   int64_t event;    /* RECORD, WAIT: 3 * step + stream of the event's step and stream
-                       (step counted over all passes); pass-end events:
-                       3 * (passes * steps per pass + pass) + stream              */
+                       (execution step counted over all passes); pass-end events:
+                       3 * (n + pass) + stream, n the larger of all plan steps and
+                       all execution steps                                         */
   int32_t space;    /* READ, WRITE: cdag_trace_space of the range                        */
   int32_t reserved;
   int64_t off;      /* READ, WRITE: byte offset in the space (STAGE: within the leaf's
@@ -417,7 +420,13 @@ int cdag_memsim(cdag_ctx* c, const int64_t* order, int64_t n, int elem_bytes,
                 int64_t* M_out, int64_t* peak_post, int64_t* peak_live);
 
 /* Host-only: build the budgeted plan for (prec, batched) on the current
- * schedule and budget.  CDAG_E_BUDGET if one step cannot fit. */
+ * schedule and budget.  CDAG_E_BUDGET if one step cannot fit.  A batched plan
+ * without evictions is executed by its data and memory dependencies:
+ * contractions of different plan steps share a launch where neither needs the
+ * other's output or memory (the statistics are the plan's).  Without a budget
+ * its placement may take up to 128 MiB per pass to make room for that
+ * (arena_bytes says so; an arena that only holds the tightest placement is
+ * taken as well). */
 int cdag_plan(cdag_ctx* c, int prec, int batched, cdag_plan_stats* out);
 
 /* The last plan's op list: op[i] in cdag_plan_op, node[i], step[i]. */

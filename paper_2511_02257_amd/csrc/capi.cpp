@@ -68,9 +68,28 @@ void ensure_plan(Ctx& c, int prec, int batched) {
   o.lookahead = c.wave_lookahead;
   o.leaves_resident = c.leaves_resident;
   o.t_chunks = c.t_chunks;
+  o.overlap = c.use_graphs == 0;
+  o.spread = c.spread;
+  // measured on the K = 64 contractions: FP64, FP32, split BF16 in two and three pieces
+  constexpr double kFlopRate[4] = {65e12, 110e12, 200e12, 140e12};
+  o.flop_rate = kFlopRate[prec];
   c.plan = make_plan(c.dag, c.order, o);
   place(c.dag, c.plan);
   c.kplan = make_kernel_plan(c.dag, c.plan, prec, c.tiles, c.fuse_traces);
+  // a plan that fits the static scratch (with its staging of the largest leaf)
+  // in the tightest placement keeps to it where the wider one would not fit
+  const int64_t wider = c.plan.halves() * (c.plan.pool_bytes - c.plan.tight_pool_bytes);
+  if (wider > 0) {
+    int64_t leaf = 0;
+    for (int64_t u = 0; u < c.dag.n_leaves; ++u)
+      leaf = std::max<int64_t>(leaf, c.dag.elems(u) * (c.leaf_dtype[u] == CDAG_C64 ? 8 : 16));
+    const int64_t need_bytes = c.kplan.total_bytes + leaf + 1024;   // 1024: the alignments of either layout
+    if (need_bytes > CDAG_STATIC_SCRATCH_BYTES && need_bytes - wider <= CDAG_STATIC_SCRATCH_BYTES + 2048) {
+      c.plan.opts.spread = false;
+      place(c.dag, c.plan);
+      c.kplan = make_kernel_plan(c.dag, c.plan, prec, c.tiles, c.fuse_traces);
+    }
+  }
   // host result buffers sized with the plan (an execute then writes them
   // without allocating)
   c.corr_host.resize(c.kplan.corr_bytes / 8);

@@ -37,6 +37,8 @@ struct Ctx {
   int64_t t_chunks = 1;
   bool fuse_traces = true;       // a step's traces ride in one of its contraction launches
   bool timing = false;
+  bool spread = true;            // plans may take more than the tightest pool (off while the bound
+                                 // arena only holds that)
   TileTable tiles;               // (prec, kind, N) -> kernel variant overrides
   uint64_t version = 1;          // bumped by every change that invalidates a plan
   // last plan

@@ -137,7 +137,7 @@ struct PlanRec {
   // EXEC: arena offsets of the left and right operands (dev_off: the output).
   int64_t a_off = -1, b_off = -1;
   // Synchronisation between the three streams (compute, upload, spill), as
-  // steps of the same chunk whose work must have finished (-1: none):
+  // execution steps of the same chunk whose work must have finished (-1: none):
   //   D2H    wait_comp: kernels that last touched the tensor;
   //          wait_h2d:  an upload that last read the host range it writes;
   //   H2D    wait_comp: kernels that last touched the arena range it writes;
@@ -146,6 +146,7 @@ struct PlanRec {
   //   ALLOC  wait_d2h:  a spill that last read the arena range (the kernels
   //                     of the step wait for it before writing the output).
   int64_t wait_comp = -1, wait_h2d = -1, wait_d2h = -1;
+  int64_t xstep = 0;             // execution step (Plan::Program)
 };
 
 struct PlanOpts {
@@ -163,6 +164,11 @@ struct PlanOpts {
   // size / t_chunks bytes under budget / 2 (the whole budget when
   // t_chunks = 1).
   int64_t t_chunks = 1;
+  bool overlap = false;    // uploads run beside kernels (eager issue), so they are worth staging
+  bool spread = true;      // place() may use more memory than the tightest pool (unlimited budget)
+  // Rates by which place() tells whether uploads or contractions bound a pass
+  // (flop/s of the precision's kernels, bytes/s of the host link).
+  double flop_rate = 65e12, link_rate = 50e9;
 };
 
 // Plan of one pass (t_chunks = 1: the whole execution).  Counters and the
@@ -175,6 +181,21 @@ struct Plan {
   int64_t peak_resident = 0, n_evict = 0, n_h2d = 0, h2d_bytes = 0, n_d2h = 0, d2h_bytes = 0;
   // placement
   int64_t pool_bytes = 0;                   // physical high-water of one pass's tensor pool
+  int64_t tight_pool_bytes = 0;             // of the tightest placement (see PlanOpts::spread)
+  // Execution steps: what the runtime issues together, the transfers and
+  // contractions of one or more plan steps (place()); records ordered by
+  // execution step, transfers first.  One program for the first pass and one
+  // for the later ones, on the same placement.
+  struct Program {
+    std::vector<PlanRec> recs;
+    std::vector<int64_t> off = {0};         // per execution step: first index in recs
+    int64_t n() const { return (int64_t)off.size() - 1; }
+  } first, later;
+  const Program& program(int64_t pass) const { return pass == 0 ? first : later; }
+  // Global number of the first execution step of a pass (pass = chunks(): all).
+  int64_t xfirst(int64_t pass) const { return pass == 0 ? 0 : first.n() + (pass - 1) * later.n(); }
+  int64_t n_xsteps() const { return xfirst(chunks()); }
+  int64_t pass_of(int64_t g) const { return g < first.n() ? 0 : 1 + (g - first.n()) / later.n(); }
   int64_t host_spill_bytes = 0;             // host spill range of one pass
   std::vector<int64_t> leaf_off;            // leaves_resident: offsets in the leaf region
   int64_t leaf_region_bytes = 0;            // whole leaves (all time slices)
@@ -195,8 +216,8 @@ std::vector<std::vector<int64_t>> cut_waves(const Dag& d, const std::vector<int6
 // Throws Error(CDAG_E_INVALID) when t_chunks < 1 or does not divide the nt of
 // every node, Error(CDAG_E_BUDGET) when a step does not fit.
 Plan make_plan(const Dag& d, const std::vector<int64_t>& order, const PlanOpts& o);
-// Assign arena offsets (256-byte aligned, best fit) and host spill offsets,
-// and derive the cross-stream waits.
+// Assign arena offsets (256-byte aligned) and host spill offsets, cut the
+// records into execution steps and derive the cross-stream waits.
 void place(const Dag& d, Plan& p);
 
 }  // namespace cdag

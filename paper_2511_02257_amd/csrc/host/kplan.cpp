@@ -4,7 +4,6 @@
 #include <algorithm>
 #include <climits>
 #include <cstring>
-#include <set>
 
 #include "../../../include/cdag.h"
 
@@ -171,7 +170,6 @@ KernelPlan make_kernel_plan(const Dag& d, const Plan& p, int prec, const TileTab
   KernelPlan kp;
   kp.prec = prec;
   const int64_t acc_bytes = prec == CDAG_FP64 ? 8 : 4;   // one real accumulator
-  const int64_t S = (int64_t)p.steps.size();
 
   // tree index of each root, correlator buffers
   std::vector<int64_t> tree_of(d.n_nodes(), -1);
@@ -208,30 +206,38 @@ KernelPlan make_kernel_plan(const Dag& d, const Plan& p, int prec, const TileTab
   // one index map per (spec, N), laid out after the descriptor tables
   std::map<std::pair<int32_t, int32_t>, int64_t> map_index;
   std::vector<IndexMap> maps;
-  // A pass covers nt / t_chunks slices; the split count follows the whole
-  // contraction (all nt slices), so it does not change with t_chunks and the
-  // results stay bit-identical.
-  auto decomp = [&](int64_t u, HecDesc& h) -> int {
+  // Each contraction's descriptor (without offsets) and kernel variant, the same
+  // in every pass.  A pass covers nt / t_chunks slices; the split count follows
+  // the whole contraction (all nt slices), so it does not change with t_chunks
+  // and the results stay bit-identical.
+  std::vector<HecDesc> proto(d.n_nodes());
+  std::vector<int> variant(d.n_nodes(), -1);
+  for (int64_t u = d.n_leaves; u < d.n_nodes(); ++u) {
+    if (d.kind[u] == HCA) continue;
     Gemm g;
     d.gemm_shape(u, &g.M, &g.N, &g.K);
     const int choice = tile_of(u);
-    decompose(g, d.nt[u], choice, prec, &h, (int)(d.nt[u] / p.chunks()));
-    if (is_spec(d.kind[u])) return kGenVariant;
-    if (tiles.count(std::make_tuple(prec, (int)d.kind[u], (int)d.nvec[u]))) return choice_variant(choice);
-    const int v = default_variant(prec, choice_variant(choice), g);
-    retile(v, &h);
-    return v;
+    proto[u] = HecDesc{};
+    decompose(g, d.nt[u], choice, prec, &proto[u], (int)(d.nt[u] / p.chunks()));
+    if (is_spec(d.kind[u])) {
+      variant[u] = kGenVariant;
+    } else if (tiles.count(std::make_tuple(prec, (int)d.kind[u], (int)d.nvec[u]))) {
+      variant[u] = choice_variant(choice);
+    } else {
+      variant[u] = default_variant(prec, choice_variant(choice), g);
+      retile(variant[u], &proto[u]);
+    }
+  }
+  auto ws_of = [&](const HecDesc& h) {
+    return h.splits > 1 ? align256((int64_t)h.splits * h.nt * 2 * h.M * h.N * acc_bytes) : 0;
   };
 
-  // pass 1: workspace size (max over steps) and descriptor counts
-  for (int64_t s = 0; s < S; ++s) {
+  // pass 1: workspace size (max over plan steps; an execution step with more
+  // runs its split contractions in several rounds of it)
+  for (const auto& step : p.steps) {
     int64_t ws = 0;
-    for (int64_t u : p.steps[s]) {
-      if (d.kind[u] == HCA) continue;
-      HecDesc h{};
-      decomp(u, h);
-      if (h.splits > 1) ws += align256((int64_t)h.splits * h.nt * 2 * h.M * h.N * acc_bytes);
-    }
+    for (int64_t u : step)
+      if (d.kind[u] != HCA) ws += ws_of(proto[u]);
     kp.ws_bytes = std::max(kp.ws_bytes, ws);
   }
   // [leaf region][half 0: tensor pool, workspace][half 1 (t_chunks > 1)]...
@@ -244,7 +250,10 @@ KernelPlan make_kernel_plan(const Dag& d, const Plan& p, int prec, const TileTab
   // pass 2: descriptors (host blob; arena offset = blob_off + host offset),
   // one set per pass over the time slices: pass k runs in half k % 2 on
   // slices [k nt / C, (k + 1) nt / C) of every tensor.
-  kp.launch_off.reserve(C * S + 1);
+  kp.launch_off.reserve(p.n_xsteps() + 1);
+  // last round (step, for traces) that an operand was counted in, per variant
+  std::vector<int64_t> hec_mark[kAllVariants], hca_mark;
+  int64_t round = 0, step_id = 0;
   for (int64_t k = 0; k < C; ++k) {
     const int64_t shift = (k % 2) * kp.half_bytes;
     // arena offset of operand x of a contraction in pass k: a resident leaf's
@@ -253,30 +262,62 @@ KernelPlan make_kernel_plan(const Dag& d, const Plan& p, int prec, const TileTab
       if (p.opts.leaves_resident && d.is_leaf(x)) return p.leaf_off[x] + k * p.tsize(d, x);
       return planned + shift;
     };
-    for (int64_t s = 0; s < S; ++s) {
+    const Plan::Program& prog = p.program(k);
+    for (int64_t s = 0; s < prog.n(); ++s) {
       const size_t step_first = kp.launches.size();
       kp.launch_off.push_back((int64_t)kp.launches.size());
       constexpr int kGroups = kAllVariants;
-      std::vector<HecDesc> hec[kGroups];
-      int64_t tiles[kGroups] = {0};
-      double v_flops[kGroups] = {0}, v_bytes[kGroups] = {0};
-      int32_t v_kinds[kGroups] = {0};
-      bool v_interior[kGroups];
-      std::fill(v_interior, v_interior + kGroups, true);
-      double red_bytes = 0, hca_flops = 0, hca_bytes = 0;
-      int32_t red_kinds = 0;
-      std::vector<RedDesc> red;
+      // Launches are collected per kernel variant in rounds: a round ends where
+      // its split contractions have filled the workspace, which the next one
+      // then uses again.
+      struct Round {
+        std::vector<HecDesc> hec[kGroups];
+        int64_t tiles[kGroups] = {0};
+        double flops[kGroups] = {0}, bytes[kGroups] = {0};
+        int32_t kinds[kGroups] = {0};
+        bool ragged[kGroups] = {false};
+        std::vector<RedDesc> red;
+        double red_bytes = 0;
+        int32_t red_kinds = 0;
+        int64_t ws_used = 0, red_items = 0;
+      } rd;
+      auto flush_round = [&] {
+        for (int tl = 0; tl < kGroups; ++tl) {
+          if (rd.hec[tl].empty()) continue;
+          Launch L{L_HEC, tl, (int32_t)rd.hec[tl].size(), 0, rd.tiles[tl], 0};
+          L.flops = rd.flops[tl];
+          L.bytes = rd.bytes[tl];
+          L.kinds = rd.kinds[tl];
+          L.interior = rd.ragged[tl] ? 0 : 1;
+          L.host_desc = (int64_t)kp.blob.size();
+          for (auto& h : rd.hec[tl]) put(kp.blob, h);
+          kp.launches.push_back(L);
+        }
+        if (!rd.red.empty()) {
+          Launch L{L_RED, 0, (int32_t)rd.red.size(), 0, rd.red_items, 0};
+          L.bytes = rd.red_bytes;
+          L.kinds = rd.red_kinds;
+          L.host_desc = (int64_t)kp.blob.size();
+          for (auto& x : rd.red) put(kp.blob, x);
+          kp.launches.push_back(L);
+        }
+        rd = Round();
+        ++round;
+      };
+      double hca_flops = 0, hca_bytes = 0;
       std::vector<HcaDesc> hca;
-      int64_t ws = kp.ws_off + shift, items = 0;
       // algorithmic bytes of a launch: each distinct operand read once, each
       // output written once (operands shared by contractions of one launch,
       // e.g. a closing meson traced against many roots, count once)
-      std::set<int64_t> v_seen[kGroups], hca_seen;
-      auto operand_bytes = [&](std::set<int64_t>& seen, int64_t x) {
-        return seen.insert(x).second ? (double)p.tsize(d, x) : 0.0;
+      auto operand_bytes = [&](std::vector<int64_t>& mark, int64_t id, int64_t x) {
+        if (mark.empty()) mark.assign(d.n_nodes(), -1);
+        if (mark[x] == id) return 0.0;
+        mark[x] = id;
+        return (double)p.tsize(d, x);
       };
-      for (int64_t ri = p.rec_off[s]; ri < p.rec_off[s + 1]; ++ri) {
-        const PlanRec& r = p.recs[ri];
+      const int64_t hca_id = step_id++;
+      for (int64_t ri = prog.off[s]; ri < prog.off[s + 1]; ++ri) {
+        const PlanRec& r = prog.recs[ri];
         if (r.op != OP_EXEC) continue;
         const int64_t u = r.node;
         const double fl = d.flops(u) / (double)C;
@@ -292,11 +333,11 @@ KernelPlan make_kernel_plan(const Dag& d, const Plan& p, int prec, const TileTab
           h.n = d.nvec[u];
           hca.push_back(h);
           hca_flops += fl;
-          hca_bytes += operand_bytes(hca_seen, d.left[u]) + operand_bytes(hca_seen, d.right[u]);
+          hca_bytes += operand_bytes(hca_mark, hca_id, d.left[u]) + operand_bytes(hca_mark, hca_id, d.right[u]);
           continue;
         }
-        HecDesc h{};
-        const int tl = decomp(u, h);
+        HecDesc h = proto[u];
+        const int tl = variant[u];
         const bool gen = tl == kGenVariant;
         h.map_off = -1;
         if (gen) {
@@ -308,58 +349,42 @@ KernelPlan make_kernel_plan(const Dag& d, const Plan& p, int prec, const TileTab
           }
           h.map_off = -2 - it->second;                   // fixed up below (needs the layout)
         }
-        const double ab = operand_bytes(v_seen[tl], d.left[u]) + operand_bytes(v_seen[tl], d.right[u]) +
-                          (double)p.tsize(d, u);
+        const int64_t ws_bytes = ws_of(h);
+        if (rd.ws_used + ws_bytes > kp.ws_bytes || rd.tiles[tl] + h.tile_count > INT32_MAX) flush_round();
+        const double ab = operand_bytes(hec_mark[tl], round, d.left[u]) +
+                          operand_bytes(hec_mark[tl], round, d.right[u]) + (double)p.tsize(d, u);
         kp.hec_flops += fl;
         kp.hec_bytes += ab;
-        v_flops[tl] += fl;
-        v_bytes[tl] += ab;
-        v_kinds[tl] |= 1 << std::min<int32_t>(d.kind[u], 7);
+        rd.flops[tl] += fl;
+        rd.bytes[tl] += ab;
+        rd.kinds[tl] |= 1 << std::min<int32_t>(d.kind[u], 7);
         h.a_off = a_off;
         h.b_off = b_off;
         h.c_off = r.dev_off + shift;
         h.ws_off = -1;
-        h.tile_begin = (int32_t)tiles[tl];
-        tiles[tl] += h.tile_count;
+        h.tile_begin = (int32_t)rd.tiles[tl];
+        rd.tiles[tl] += h.tile_count;
         if (gen || !hec_interior(h, kTileShapes[variant_tile(tl)].bm, kTileShapes[variant_tile(tl)].bn, k_step(prec)))
-          v_interior[tl] = false;
+          rd.ragged[tl] = true;
         kp.hec_items += h.tile_count;
         if (h.splits > 1) {
-          h.ws_off = ws;
-          RedDesc rd{};
-          rd.ws_off = ws;
-          rd.c_off = h.c_off;
-          rd.mn = h.M * h.N;
-          rd.nt = h.nt;
-          rd.splits = h.splits;
-          rd.item_begin = (int32_t)items;
-          items += (2LL * rd.nt * rd.mn + 255) / 256;
-          red.push_back(rd);
-          red_bytes += 2.0 * rd.nt * (double)rd.mn * ((double)rd.splits * acc_bytes + elem_bytes_of(prec));
-          red_kinds |= 1 << d.kind[u];
-          ws += align256((int64_t)h.splits * h.nt * 2 * h.M * h.N * acc_bytes);
+          h.ws_off = kp.ws_off + shift + rd.ws_used;
+          RedDesc e{};
+          e.ws_off = h.ws_off;
+          e.c_off = h.c_off;
+          e.mn = h.M * h.N;
+          e.nt = h.nt;
+          e.splits = h.splits;
+          e.item_begin = (int32_t)rd.red_items;
+          rd.red_items += (2LL * e.nt * e.mn + 255) / 256;
+          rd.red.push_back(e);
+          rd.red_bytes += 2.0 * e.nt * (double)e.mn * ((double)e.splits * acc_bytes + elem_bytes_of(prec));
+          rd.red_kinds |= 1 << d.kind[u];
+          rd.ws_used += ws_bytes;
         }
-        hec[tl].push_back(h);
+        rd.hec[tl].push_back(h);
       }
-      for (int tl = 0; tl < kGroups; ++tl) {
-        if (hec[tl].empty()) continue;
-        Launch L{L_HEC, tl, (int32_t)hec[tl].size(), 0, tiles[tl], 0};
-        L.flops = v_flops[tl];
-        L.bytes = v_bytes[tl];
-        L.kinds = v_kinds[tl];
-        L.interior = v_interior[tl] ? 1 : 0;
-        L.host_desc = (int64_t)kp.blob.size();
-        for (auto& h : hec[tl]) put(kp.blob, h);
-        kp.launches.push_back(L);
-      }
-      if (!red.empty()) {
-        Launch L{L_RED, 0, (int32_t)red.size(), 0, items, 0};
-        L.bytes = red_bytes;
-        L.kinds = red_kinds;
-        L.host_desc = (int64_t)kp.blob.size();
-        for (auto& x : red) put(kp.blob, x);
-        kp.launches.push_back(L);
-      }
+      flush_round();
       if (!hca.empty()) {
         int64_t n_titems = 0;
         for (auto& h : hca) { h.item_begin = (int32_t)n_titems; n_titems += h.nt; }

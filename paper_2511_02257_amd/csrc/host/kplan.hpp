@@ -86,8 +86,8 @@ constexpr int kSplitTarget = 512, kMinKSplit = 256;
 struct KernelPlan {
   int prec = 0;
   int64_t chunks = 1;                // passes over the time slices (PlanOpts::t_chunks)
-  std::vector<int64_t> launch_off;   // per step of each pass (k * n_steps + s): first launch index
-                                     // (size chunks * n_steps + 1)
+  std::vector<int64_t> launch_off;   // per execution step of each pass (global number): first launch
+                                     // index (size n_xsteps + 1)
   std::vector<Launch> launches;
   Launch xsum{};
   int64_t xsum_entries_off = 0;     // arena offset of the XsumEntry table

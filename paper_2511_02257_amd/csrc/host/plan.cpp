@@ -217,9 +217,17 @@ class Pool {
   std::set<std::pair<int64_t, int64_t>> by_size;  // (size, offset)
 
   // Returns offset; *comp / *copy receive the waits inherited from the block.
-  int64_t alloc(int64_t bytes, int64_t* comp, int64_t* copy) {
+  // Best fit; while the pool is below `cap`, fresh memory first, and then the
+  // large enough block whose last use is oldest.
+  int64_t alloc(int64_t bytes, int64_t* comp, int64_t* copy, int64_t cap = 0) {
     bytes = align_up(std::max<int64_t>(bytes, 1));
     auto it = by_size.lower_bound({bytes, -1});
+    if (cap > 0 && top + bytes <= cap) {
+      it = by_size.end();
+    } else if (cap > 0) {
+      for (auto k = it; k != by_size.end(); ++k)
+        if (free_[k->second].comp < free_[it->second].comp) it = k;
+    }
     if (it != by_size.end()) {
       int64_t off = it->second;
       Free f = free_[off];
@@ -231,7 +239,7 @@ class Pool {
       return off;
     }
     // extend from a free block that ends at the top, else from fresh memory
-    if (!free_.empty()) {
+    if (!free_.empty() && !(cap > 0 && top + bytes <= cap)) {
       auto last = std::prev(free_.end());
       if (last->first + last->second.size == top) {
         int64_t off = last->first;
@@ -277,28 +285,73 @@ class Pool {
 };
 }  // namespace
 
-void place(const Dag& d, Plan& p) {
+namespace {
+// Memory that placement may take beyond the tightest pool to keep contractions
+// of different plan steps from waiting for one another's memory: half of the
+// 256 MB last-level cache, so that intermediates still meet there.
+constexpr int64_t kSpreadBytes = 128LL << 20;
+// Uploads of one execution step in overlapping issue: at least this, and a
+// quarter of what the plan step uploads.
+constexpr int64_t kStageBytes = 32LL << 20;
+
+// How execution steps are cut (place()).
+enum Cut { PLAN_STEPS, STAGED, MERGED };
+
+// One placement of the pool, with at most `cap` bytes of it taken before memory
+// is reused (0: tightest; the offsets then do not depend on the cut), and its
+// program.  *staged (may be nullptr): whether a step's uploads are staged.
+Plan::Program place_pool(const Dag& d, Plan& p, int64_t base, int64_t cap, Cut cut, bool* staged = nullptr) {
   const int64_t n = d.n_nodes();
-  const int eb = p.opts.elem_bytes;
-  p.leaf_off.assign(d.n_leaves, -1);
-  int64_t base = 0;
-  if (p.opts.leaves_resident) {
-    // whole leaves: every pass reads its own slices of them
-    for (int64_t u = 0; u < d.n_leaves; ++u) {
-      p.leaf_off[u] = base;
-      base += align_up(d.size(u, eb));
-    }
-  }
-  p.leaf_region_bytes = base;
+  const bool merge = cut != PLAN_STEPS;
   Pool dev, host;
-  // last_touch: step of the last kernels that read or wrote the tensor;
-  // spilled: step of the spill that wrote its host copy; uploaded: step of the
-  // last upload that read that host copy
+  // last_touch: execution step of the last kernels that read or wrote the
+  // tensor; spilled: that of the spill that wrote its host copy; uploaded: that
+  // of the last upload that read that host copy; avail: first one whose kernels
+  // may read it; out_after: first one whose kernels may write it
   std::vector<int64_t> off(n, -1), hoff(n, -1), last_touch(n, -1), spilled(n, -1), uploaded(n, -1);
+  std::vector<int64_t> avail(n, 0), out_after(n, 0), in_step;
   if (p.opts.leaves_resident)
     for (int64_t u = 0; u < d.n_leaves; ++u) off[u] = p.leaf_off[u];
-  for (PlanRec& r : p.recs) {
+  // A step with more uploads than one stage stages its smaller tensors first (a
+  // contraction's small operand then does not hold it back): stage of each of
+  // its uploads, -1 for the uploads of other steps.
+  const int64_t R = (int64_t)p.recs.size();
+  std::vector<int64_t> stage(p.steps.size(), INT64_MAX), stage_of(R, -1);
+  for (size_t s = 0; merge && p.opts.overlap && s < p.steps.size(); ++s) {
+    std::vector<int64_t> ups;
+    int64_t bytes = 0, in_stage = 0, k = 0;
+    for (int64_t i = p.rec_off[s]; i < p.rec_off[s + 1]; ++i)
+      if (p.recs[i].op == OP_H2D) {
+        bytes += p.tsize(d, p.recs[i].node);
+        ups.push_back(i);
+      }
+    stage[s] = std::max<int64_t>(kStageBytes, bytes / 4);
+    if (bytes <= stage[s]) continue;
+    if (staged) *staged = true;
+    std::stable_sort(ups.begin(), ups.end(), [&](int64_t a, int64_t b) {
+      return p.tsize(d, p.recs[a].node) < p.tsize(d, p.recs[b].node);
+    });
+    for (int64_t i : ups) {
+      const int64_t sz = p.tsize(d, p.recs[i].node);
+      if (in_stage > 0 && in_stage + sz > stage[s]) {
+        ++k;
+        in_stage = 0;
+      }
+      in_stage += sz;
+      stage_of[i] = k;
+    }
+  }
+  int64_t up_x = 0, up_bytes = 0, last_x = -1;
+  int64_t floor_x = 0, cur = -1, base_x = 0;   // STAGED: first execution step of plan step `cur`; its first upload's
+  for (int64_t i = 0; i < R; ++i) {
+    PlanRec& r = p.recs[i];
     const int64_t x = r.node, s = r.step, sz = p.tsize(d, x);
+    if (s != cur) {
+      cur = s;
+      if (cut == STAGED) floor_x = last_x + 1;
+      base_x = std::max(up_x, floor_x);
+    }
+    r.xstep = s;
     switch (r.op) {
       case OP_D2H: {
         int64_t c0, up;
@@ -319,7 +372,7 @@ void place(const Dag& d, Plan& p) {
         break;
       case OP_H2D: {
         int64_t comp, spill;
-        off[x] = base + dev.alloc(sz, &comp, &spill);
+        off[x] = base + dev.alloc(sz, &comp, &spill, cap);
         r.dev_off = off[x];
         r.wait_comp = comp;          // kernels that last touched this memory
         if (d.is_leaf(x)) {
@@ -330,25 +383,46 @@ void place(const Dag& d, Plan& p) {
           r.wait_d2h = std::max(spill, spilled[x]);   // ... and the spill that wrote the host copy
           uploaded[x] = s;
         }
+        if (merge) {
+          int64_t at = std::max({up_x, floor_x, comp + 1});
+          if (stage_of[i] >= 0) at = std::max(base_x + stage_of[i], comp + 1);
+          else if (at == up_x && up_bytes > 0 && up_bytes > stage[s] - sz) ++at;
+          if (at > up_x) {
+            up_bytes = 0;
+            up_x = at;
+          }
+          up_bytes += sz;
+          r.xstep = avail[x] = at;
+        }
         break;
       }
       case OP_ALLOC: {
         int64_t comp, spill;
-        off[x] = base + dev.alloc(sz, &comp, &spill);
+        off[x] = base + dev.alloc(sz, &comp, &spill, cap);
         r.dev_off = off[x];
         r.wait_d2h = spill;          // a spill that last read this memory
+        out_after[x] = comp + 1;     // kernels that last touched this memory
         break;
       }
-      case OP_EXEC:
-        r.a_off = off[d.left[x]];
-        r.b_off = off[d.right[x]];
+      case OP_EXEC: {
+        const int64_t a = d.left[x], b = d.right[x];
+        r.a_off = off[a];
+        r.b_off = off[b];
         r.dev_off = d.kind[x] == HCA ? -1 : off[x];
-        last_touch[d.left[x]] = s;
-        last_touch[d.right[x]] = s;
-        last_touch[x] = s;
+        if (merge) {
+          int64_t at = std::max({avail[a], avail[b], out_after[x], floor_x});
+          if ((int64_t)in_step.size() <= at) in_step.resize(at + 1, 0);
+          while (in_step[at] >= p.opts.wave_max)
+            if (++at == (int64_t)in_step.size()) in_step.push_back(0);
+          ++in_step[at];
+          r.xstep = at;
+          avail[x] = at + 1;
+        }
+        for (int64_t u : {a, b, x}) last_touch[u] = std::max(last_touch[u], r.xstep);
         break;
+      }
       case OP_FREE:
-        dev.release(off[x] - base, sz, s, -1);
+        dev.release(off[x] - base, sz, merge ? last_touch[x] : s, -1);
         off[x] = -1;
         if (hoff[x] >= 0) {
           host.release(hoff[x], sz, -1, uploaded[x]);
@@ -357,9 +431,98 @@ void place(const Dag& d, Plan& p) {
         }
         break;
     }
+    if (r.op == OP_EXEC || r.op == OP_H2D || r.op == OP_D2H) last_x = std::max(last_x, r.xstep);
   }
   p.pool_bytes = dev.top;
   p.host_spill_bytes = host.top;
+
+  // An ALLOC has no work of its own; it goes with its contraction, whose
+  // kernels wait for what it waits for.
+  std::vector<int64_t> exec_x(n, -1);
+  for (const PlanRec& r : p.recs)
+    if (r.op == OP_EXEC) exec_x[r.node] = r.xstep;
+  if (merge)
+    for (PlanRec& r : p.recs)
+      if (r.op == OP_ALLOC) r.xstep = exec_x[r.node];
+  const int64_t X = merge ? last_x + 1 : (int64_t)p.steps.size();
+  Plan::Program g;
+  g.off.assign(X + 1, 0);
+  auto issued = [](const PlanRec& r) { return r.op != OP_DROP && r.op != OP_FREE; };
+  for (const PlanRec& r : p.recs)
+    if (issued(r)) ++g.off[r.xstep + 1];
+  for (int64_t k = 0; k < X; ++k) g.off[k + 1] += g.off[k];
+  g.recs.resize(g.off[X]);
+  std::vector<int64_t> at(g.off.begin(), g.off.end() - 1);
+  for (bool transfers : {true, false})
+    for (const PlanRec& r : p.recs)
+      if (issued(r) && (r.op == OP_D2H || r.op == OP_H2D) == transfers) g.recs[at[r.xstep]++] = r;
+  return g;
+}
+}  // namespace
+
+// Execution steps.  A plan that runs in waves and never evicts need not be
+// issued plan step by plan step (the plan's steps, counters and resident peak do
+// not change):
+//   MERGED  by data and memory dependencies: a contraction joins the first
+//     execution step that is after its operands' kernels, its leaves' uploads
+//     and the kernels that last touched the memory of its output; an upload goes
+//     as early as its memory is free, in the plan's order.  Taken where that
+//     makes fewer steps.  With lookahead 0 a wave ends at the first contraction
+//     that needs one of its outputs, so a plan has hundreds of steps of a few
+//     contractions each, at about 7 us of launch and latency a step, where the
+//     dependencies are a few levels deep (46 graphs over any index pairs at N =
+//     9: 72 plan steps, 4 execution steps, a pass 733 -> 96 us; 710 rank-4
+//     graphs at N = 16 in two passes: 554 -> 30 steps, 17.2 -> 5.5 ms).
+//   STAGED  a plan step with large uploads that run beside kernels in several
+//     execution steps, each with a stage of the uploads and the contractions
+//     whose operands are there by then, so that kernels start before the last
+//     leaf.
+// A plan step with staged uploads: the first pass over the time slices is
+// MERGED, which also moves later plan steps' contractions up between the stages.
+// So are later passes where the uploads take longer than the contractions, as
+// only the work after the last upload then counts (five N families in two
+// passes, 0.88 GB of leaves: 24.0 ms by plan steps, 22.0 with the second pass
+// STAGED, 19.1 MERGED).  Else the uploads of a pass hide behind the pass before,
+// and a launch of few long items (K33) cut into several leaves compute units
+// idle in each (headline in 8 passes: 37.9 ms by plan steps, 44 with every pass
+// MERGED, 36.6 with the later ones STAGED).
+void place(const Dag& d, Plan& p) {
+  p.leaf_off.assign(d.n_leaves, -1);
+  int64_t base = 0;
+  if (p.opts.leaves_resident) {
+    // whole leaves: every pass reads its own slices of them
+    for (int64_t u = 0; u < d.n_leaves; ++u) {
+      p.leaf_off[u] = base;
+      base += align_up(d.size(u, p.opts.elem_bytes));
+    }
+  }
+  p.leaf_region_bytes = base;
+  p.first = place_pool(d, p, base, 0, PLAN_STEPS);
+  p.tight_pool_bytes = p.pool_bytes;
+  if (p.opts.batched && p.n_evict == 0) {
+    // merged where that makes fewer steps, in the tightest pool or else (without
+    // a budget) in a wider one
+    bool staged = false;
+    Plan::Program merged = place_pool(d, p, base, 0, MERGED, &staged);
+    if (p.opts.spread && p.opts.budget == INT64_MAX && p.pool_bytes < kSpreadBytes && merged.n() > 1) {
+      Plan::Program wider = place_pool(d, p, base, kSpreadBytes, MERGED);
+      if (wider.n() < std::min(merged.n(), p.first.n())) merged = std::move(wider);
+      else place_pool(d, p, base, 0, PLAN_STEPS);   // back to the tightest placement
+    }
+    if (merged.n() < p.first.n()) {
+      p.first = std::move(merged);
+    } else if (staged) {
+      p.first = std::move(merged);
+      double flops = 0;
+      for (int64_t u = d.n_leaves; u < d.n_nodes(); ++u) flops += d.flops(u);
+      const double t_pass = flops / (double)p.chunks() / p.opts.flop_rate;
+      if ((double)p.h2d_bytes / p.opts.link_rate < t_pass) {
+        p.later = place_pool(d, p, base, 0, STAGED);
+        return;
+      }
+    }
+  }
+  p.later = p.first;
 }
 
 }  // namespace cdag

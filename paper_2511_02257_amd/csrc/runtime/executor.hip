@@ -27,6 +27,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <cstdlib>
 #include <thread>
@@ -56,9 +57,9 @@ double now() {
 
 // Stream roles; trace records and event ids use these numbers.
 enum StreamRole : int { S_COMP = 0, S_H2D = 1, S_D2H = 2, kStreams = 3 };
-// Most bytes of a step's transfers, in one direction, that eager issue moves by
-// a kernel.
-constexpr int64_t kEagerMoveBytes = 8 << 20;
+// Most bytes of a step's transfers, in one direction, that are moved by a kernel
+// where copies can run beside kernels (eager issue and the three-stream graph).
+constexpr int64_t kKernelMoveBytes = 8 << 20;
 }  // namespace
 
 // ---------------------------------------------------------------- static scratch
@@ -125,6 +126,7 @@ struct Device {
   int graph_mode = 0;
   void* graph_spill = nullptr;
   void* graph_results = nullptr;
+  bool graph_finished = true;       // the last graph ends with the cross sums
 
   void drop_graphs() {
     for (auto g : seg_exec) ignore(hipGraphExecDestroy(g));
@@ -214,6 +216,21 @@ void device_bind_arena(Ctx& c, void* arena, uint64_t bytes) {
   c.dev->arena = (char*)arena;
   c.dev->arena_bytes = bytes;
   c.dev->arena_epoch++;
+  if (!c.spread) {
+    c.spread = true;
+    c.version++;
+  }
+}
+
+// Plan for (prec, batched), in the tightest placement where the bound arena
+// does not hold the wider one.
+static void plan_for_arena(Ctx& c, int prec, int batched) {
+  ensure_plan(c, prec, batched);
+  if ((uint64_t)c.kplan.total_bytes > c.dev->arena_bytes && c.plan.pool_bytes > c.plan.tight_pool_bytes) {
+    c.spread = false;
+    c.version++;
+    ensure_plan(c, prec, batched);
+  }
 }
 
 namespace {
@@ -372,7 +389,7 @@ struct PassMap {
   }
 };
 
-// Walk global steps [g0, g1), g = k * S + s being step s of pass k: each
+// Walk global execution steps [g0, g1), step s of pass k's program at a time: each
 // step's spills (after the kernels that last touched the tensor and any upload
 // still reading the host range), its uploads (after the kernels and spills
 // that last used the arena range, and the spill that wrote a re-uploaded
@@ -386,7 +403,7 @@ struct PassMap {
 template <class Ops>
 int64_t walk_steps(const Ctx& c, int64_t g0, int64_t g1, bool one_stream, bool in_capture, Ops& ops) {
   const Plan& p = c.plan;
-  const int64_t S = (int64_t)p.steps.size(), C = p.chunks();
+  const int64_t C = p.chunks();
   // waited[to][from]: newest step of stream `from` that stream `to` has waited
   // for; events of one stream complete in step order, so older ones are implied
   int64_t waited[kStreams][kStreams];
@@ -399,10 +416,11 @@ int64_t walk_steps(const Ctx& c, int64_t g0, int64_t g1, bool one_stream, bool i
   };
   int64_t n_launch = 0;
   for (int64_t g = g0; g < g1; ++g) {
-    const int64_t k = g / S, s = g % S, kS = k * S;
+    const int64_t k = p.pass_of(g), kS = p.xfirst(k), s = g - kS;
+    const Plan::Program& prog = p.program(k);
     const PassMap m(c, k);
     auto at = [&](int64_t step) { return step >= 0 ? kS + step : -1; };
-    if (s == 0 && k >= 2 && !one_stream && !(in_capture && (k - 1) * S <= g0)) {
+    if (s == 0 && k >= 2 && !one_stream && !(in_capture && p.xfirst(k - 1) <= g0)) {
       // pass k - 2 used the same half of the arena and of the spill pool
       ops.wait_pass(S_H2D, S_COMP, k - 2, g);
       ops.wait_pass(S_H2D, S_D2H, k - 2, g);
@@ -411,8 +429,8 @@ int64_t walk_steps(const Ctx& c, int64_t g0, int64_t g1, bool one_stream, bool i
     }
     bool any_d2h = false, any_h2d = false;
     int64_t alloc_d2h = -1;
-    for (int64_t ri = p.rec_off[s]; ri < p.rec_off[s + 1]; ++ri) {
-      const PlanRec& r = p.recs[ri];
+    for (int64_t ri = prog.off[s]; ri < prog.off[s + 1]; ++ri) {
+      const PlanRec& r = prog.recs[ri];
       if (r.op != OP_D2H) continue;
       wait(S_D2H, S_COMP, at(r.wait_comp));
       wait(S_D2H, S_H2D, at(r.wait_h2d));
@@ -420,8 +438,8 @@ int64_t walk_steps(const Ctx& c, int64_t g0, int64_t g1, bool one_stream, bool i
       any_d2h = true;
     }
     if (any_d2h && !one_stream) ops.record(S_D2H, g);
-    for (int64_t ri = p.rec_off[s]; ri < p.rec_off[s + 1]; ++ri) {
-      const PlanRec& r = p.recs[ri];
+    for (int64_t ri = prog.off[s]; ri < prog.off[s + 1]; ++ri) {
+      const PlanRec& r = prog.recs[ri];
       if (r.op == OP_H2D) {
         wait(S_H2D, S_COMP, at(r.wait_comp));
         wait(S_H2D, S_D2H, at(r.wait_d2h));
@@ -437,7 +455,7 @@ int64_t walk_steps(const Ctx& c, int64_t g0, int64_t g1, bool one_stream, bool i
     n_launch += ops.launch(g, m);
     if (!one_stream) {
       ops.record(S_COMP, g);
-      if (s == S - 1 && k + 2 < C)
+      if (s == prog.n() - 1 && k + 2 < C)
         for (int r = 0; r < kStreams; ++r) ops.record_pass(r, k, g);
     }
   }
@@ -485,7 +503,7 @@ struct HipOps {
   void flush(int r) {
     int64_t bytes = 0;
     for (const Move& mv : moves[r]) bytes += mv.bytes;
-    if (bytes <= kEagerMoveBytes && !(D.spill_pageable && D.spill)) {
+    if (bytes <= kKernelMoveBytes && !(D.spill_pageable && D.spill)) {
       HIPC(launch_moves(moves[r].data(), (int)moves[r].size(), st[r]));
     } else {
       for (const Move& mv : moves[r]) copy(r, mv);
@@ -565,7 +583,7 @@ struct TraceOps {
     return r;
   }
   int64_t pass_event(int64_t k, int r) const {
-    return kStreams * (c.plan.chunks() * (int64_t)c.plan.steps.size() + k) + r;
+    return kStreams * (std::max(c.plan.n_xsteps(), c.plan.chunks() * (int64_t)c.plan.steps.size()) + k) + r;
   }
   void event(int32_t op, int32_t stream, int64_t id, int64_t g) {
     cdag_trace_rec r = blank(op, stream, g);
@@ -585,8 +603,8 @@ struct TraceOps {
   void record(int r, int64_t g) { event(CDAG_TR_RECORD, r, kStreams * g + r, g); }
   void wait_pass(int to, int from, int64_t k, int64_t g) { event(CDAG_TR_WAIT, to, pass_event(k, from), g); }
   void record_pass(int r, int64_t k, int64_t g) { event(CDAG_TR_RECORD, r, pass_event(k, r), g); }
-  void transfer(const PlanRec& r, const PassMap& m, int64_t g) {
-    const int64_t bytes = m.bytes(r.node);
+  void transfer(const PlanRec& r, const PassMap& m, int64_t) {
+    const int64_t bytes = m.bytes(r.node), g = m.k * (int64_t)c.plan.steps.size() + r.step;   // its plan step
     if (r.op == OP_D2H) {
       access(CDAG_TR_READ, S_D2H, g, r.node, CDAG_SPACE_ARENA, m.dev(r.dev_off), bytes);
       access(CDAG_TR_WRITE, S_D2H, g, r.node, CDAG_SPACE_SPILL, m.host(r.host_off), bytes);
@@ -599,9 +617,10 @@ struct TraceOps {
   }
   int64_t launch(int64_t g, const PassMap& m) {
     const Plan& p = c.plan;
-    const int64_t S = (int64_t)p.steps.size(), s = g % S;
-    for (int64_t ri = p.rec_off[s]; ri < p.rec_off[s + 1]; ++ri) {
-      const PlanRec& r = p.recs[ri];
+    const Plan::Program& prog = p.program(m.k);
+    const int64_t s = g - p.xfirst(m.k);
+    for (int64_t ri = prog.off[s]; ri < prog.off[s + 1]; ++ri) {
+      const PlanRec& r = prog.recs[ri];
       if (r.op != OP_EXEC) continue;
       const int64_t* ch = c.dag.children_begin(r.node);
       access(CDAG_TR_READ, S_COMP, g, ch[0], CDAG_SPACE_ARENA, m.operand(ch[0], r.a_off), m.bytes(ch[0]));
@@ -615,10 +634,13 @@ struct TraceOps {
 };
 
 // The graph form: the same walk adding the transfers and kernels to a HIP
-// graph as nodes with explicit dependencies (no stream capture).  A node
-// depends on the previous node of its stream and on the nodes its stream
-// waited for since; an event stands for its stream's last node (joined with
-// that stream's pending waits) at the time it is recorded.
+// graph as nodes with explicit dependencies (no stream capture).  A copy node
+// depends on the previous node of its stream and on the nodes its stream waited
+// for since; an event stands for its stream's last node (joined with that
+// stream's pending waits) at the time it is recorded.  Kernels, and a step's
+// small transfers (moved by a kernel), form one chain, the compute stream's: a
+// chain node depends on the one before it and on what it needs outside the
+// chain only, so a graph without copy nodes is a plain sequence.
 struct GraphOps {
   const Ctx& c;
   Device& D;
@@ -630,28 +652,42 @@ struct GraphOps {
   std::vector<hipGraphNode_t> pass_node[kStreams];   // per pass
   std::vector<hipGraphNode_t> deps;
   std::vector<Move> moves[kStreams];                 // of the step, not yet added
+  std::set<hipGraphNode_t> chain;                    // the chain's nodes
+  bool copies = false;                               // a copy node was added
 
   GraphOps(const Ctx& ctx, Device& dev, int p, hipGraph_t g) : c(ctx), D(dev), prec(p), graph(g) {
-    const size_t G = (size_t)(ctx.plan.chunks() * (int64_t)ctx.plan.steps.size());
+    const size_t G = (size_t)ctx.plan.n_xsteps();
     for (int r = 0; r < kStreams; ++r) {
       ev_node[r].assign(G, nullptr);
       pass_node[r].assign((size_t)ctx.plan.chunks(), nullptr);
     }
   }
-  void deps_of(int r) {
-    deps = pending[r];
-    if (last[r]) deps.push_back(last[r]);
+  void need(hipGraphNode_t n, bool in_chain) {
+    if (!n || (in_chain && n != last[S_COMP] && chain.count(n))) return;
+    if (std::find(deps.begin(), deps.end(), n) == deps.end()) deps.push_back(n);
   }
-  void added(int r, hipGraphNode_t n) {
-    last[r] = n;
-    pending[r].clear();
+  // dependencies of stream r's next node; a chain node also follows the chain
+  void deps_of(int r, bool in_chain) {
+    deps.clear();
+    if (in_chain) need(last[S_COMP], true);
+    for (int q : {r, in_chain ? (int)S_COMP : r}) {
+      for (hipGraphNode_t n : pending[q]) need(n, in_chain);
+      need(last[q], in_chain);
+    }
+  }
+  void added(int r, hipGraphNode_t n, bool in_chain) {
+    for (int q : {r, in_chain ? (int)S_COMP : r}) {
+      last[q] = n;
+      pending[q].clear();
+    }
+    if (in_chain) chain.insert(n);
   }
   hipGraphNode_t head(int r) {
     if (pending[r].empty()) return last[r];
-    deps_of(r);
+    deps_of(r, r == S_COMP);
     hipGraphNode_t n = nullptr;
     HIPC(hipGraphAddEmptyNode(&n, graph, deps.data(), deps.size()));
-    added(r, n);
+    added(r, n, r == S_COMP);
     return n;
   }
   void wait(int to, int from, int64_t g, int64_t) {
@@ -668,8 +704,24 @@ struct GraphOps {
   void transfer(const PlanRec& r, const PassMap& m, int64_t) {
     moves[r.op == OP_D2H ? S_D2H : S_H2D].push_back(move_of(c, D, prec, r, m));
   }
-  // one node per kMaxMoves of the step's transfers of stream r
+  // Small transfers of the step on stream r go into the chain, one kernel node
+  // per kMaxMoves; large ones are copy nodes beside it (headline in 8 passes:
+  // 57 ms, as kernels 65).
   void flush(int r) {
+    int64_t bytes = 0;
+    for (const Move& mv : moves[r]) bytes += mv.bytes;
+    if (bytes > kKernelMoveBytes) {
+      for (const Move& mv : moves[r]) {
+        deps_of(r, false);
+        hipGraphNode_t n = nullptr;
+        HIPC(hipGraphAddMemcpyNode1D(&n, graph, deps.data(), deps.size(), mv.dst, mv.src, (size_t)mv.bytes,
+                                     r == S_D2H ? hipMemcpyDeviceToHost : hipMemcpyHostToDevice));
+        added(r, n, false);
+        copies = true;
+      }
+      moves[r].clear();
+      return;
+    }
     for (size_t done = 0; done < moves[r].size();) {
       MoveBatch mb;
       const int k = make_moves(moves[r].data() + done, (int)(moves[r].size() - done), &mb);
@@ -688,10 +740,10 @@ struct GraphOps {
     np.sharedMemBytes = 0;
     np.kernelParams = args;
     np.extra = nullptr;
-    deps_of(r);
+    deps_of(r, true);
     hipGraphNode_t n = nullptr;
     HIPC(hipGraphAddKernelNode(&n, graph, deps.data(), deps.size(), &np));
-    added(r, n);
+    added(r, n, true);
   }
   void kernel(KernelCall& k) {
     k.bind();
@@ -706,10 +758,10 @@ struct GraphOps {
     }
     return kp.launch_off[g + 1] - kp.launch_off[g];
   }
-  // the cross sums, after every stream's work
+  // The cross sums end a graph that is one chain; with copy nodes beside it
+  // they are launched after the graph.
   void finish() {
-    for (int r : {S_H2D, S_D2H})
-      if (hipGraphNode_t n = head(r)) pending[S_COMP].push_back(n);
+    if (copies) return;
     KernelCall k;
     HIPC(finish_call(c.kplan, D.arena, (char*)D.results, &k));
     kernel(k);
@@ -730,6 +782,7 @@ constexpr int64_t kSegmentSteps = 64;   // steps per one-stream graph when trans
 int64_t device_autotune(Ctx& c, int prec, int batched, int reps, bool uniform) {
   Device& D = *c.dev;
   HIPC(hipSetDevice(D.device));
+  plan_for_arena(c, prec, batched);
   const Plan& p = c.plan;
   const KernelPlan& kp = c.kplan;
   if (!D.arena) throw Error(CDAG_E_STATE, "cdag_bind_arena first");
@@ -866,7 +919,7 @@ int64_t device_autotune_insitu(Ctx& c, int prec, int batched, int reps) {
         }
         c.tiles[key] = v;
         c.version++;
-        ensure_plan(c, prec, batched);
+        plan_for_arena(c, prec, batched);
         if ((uint64_t)c.kplan.total_bytes > c.dev->arena_bytes) continue;
         double t = 1e300;                        // fastest of the reps (robust to noise)
         for (int r = 0; r < reps; ++r) {
@@ -900,7 +953,7 @@ int64_t device_autotune_insitu(Ctx& c, int prec, int batched, int reps) {
 void trace_execute(const Ctx& c, int prec, std::vector<cdag_trace_rec>& out, int64_t fail_at) {
   out.clear();
   TraceOps ops{c, prec, out, fail_at};
-  walk_steps(c, 0, c.plan.chunks() * (int64_t)c.plan.steps.size(), false, false, ops);
+  walk_steps(c, 0, c.plan.n_xsteps(), false, false, ops);
 }
 
 namespace {
@@ -923,14 +976,16 @@ hipGraph_t capture_steps(Ctx& c, Device& D, int prec, int64_t g0, int64_t g1, bo
 }
 
 // Build the whole step sequence as one graph over the three streams' work,
-// with the plan's waits as explicit edges.
-hipGraph_t build_graph(Ctx& c, Device& D, int prec) {
+// with the plan's waits as explicit edges.  *finished: whether it ends with the
+// cross sums.
+hipGraph_t build_graph(Ctx& c, Device& D, int prec, bool* finished) {
   hipGraph_t g = nullptr;
   HIPC(hipGraphCreate(&g, 0));
   try {
     GraphOps ops(c, D, prec, g);
-    walk_steps(c, 0, c.plan.chunks() * (int64_t)c.plan.steps.size(), false, false, ops);
+    walk_steps(c, 0, c.plan.n_xsteps(), false, false, ops);
     ops.finish();
+    *finished = !ops.copies;
   } catch (...) {
     ignore(hipGraphDestroy(g));
     throw;
@@ -940,10 +995,10 @@ hipGraph_t build_graph(Ctx& c, Device& D, int prec) {
 }  // namespace
 
 void device_execute(Ctx& c, int prec, int batched, cdag_exec_stats* st) {
-  (void)batched;
   Device& D = *c.dev;
   const double tw0 = now();
   HIPC(hipSetDevice(D.device));
+  if (D.arena) plan_for_arena(c, prec, batched);
   const Plan& p = c.plan;
   const KernelPlan& kp = c.kplan;
   if (!D.arena) throw Error(CDAG_E_STATE, "cdag_bind_arena first");
@@ -954,7 +1009,7 @@ void device_execute(Ctx& c, int prec, int batched, cdag_exec_stats* st) {
   ensure_stage(c, prec);
   ensure_spill(D, p.halves() * p.host_spill_bytes);
   ensure_pinned(D.results, D.results_bytes, kp.corr_bytes + kp.sums_bytes);
-  const int64_t S = (int64_t)p.steps.size(), G = p.chunks() * S;
+  const int64_t G = p.n_xsteps();
   ensure_events(D, (size_t)std::max<int64_t>(G, 1), (size_t)p.chunks());
 
   // descriptor tables: one upload per (plan, arena)
@@ -993,17 +1048,19 @@ void device_execute(Ctx& c, int prec, int batched, cdag_exec_stats* st) {
   if (graphs) {
     // replay graphs: one-stream segments of kSegmentSteps steps when there are
     // transfers (else one), or one graph built over the three streams; the
-    // cross sums are the last one's last node (launched after the graphs they
-    // started 23 us after the last step's kernels)
+    // cross sums are the last one's last node where it has no copy nodes
+    // (launched after the graphs they started 23 us after the last kernels)
     const bool one = c.use_graphs == 1;
     const int64_t seg = one && has_copies ? kSegmentSteps : std::max<int64_t>(G, 1);
     if (D.graph_key != pkey || D.graph_epoch != D.arena_epoch || D.graph_spill != D.spill ||
         D.graph_stage != D.stage_version[prec] || D.graph_mode != c.use_graphs || D.graph_results != D.results) {
       D.drop_graphs();
+      D.graph_finished = true;
       for (int64_t g0 = 0; g0 == 0 || g0 < G; g0 += seg) {
         hipGraph_t g = nullptr;
         try {
-          g = one ? capture_steps(c, D, prec, g0, std::min(G, g0 + seg), g0 + seg >= G) : build_graph(c, D, prec);
+          g = one ? capture_steps(c, D, prec, g0, std::min(G, g0 + seg), g0 + seg >= G)
+                  : build_graph(c, D, prec, &D.graph_finished);
         } catch (...) {
           D.drop_graphs();
           throw;
@@ -1021,6 +1078,7 @@ void device_execute(Ctx& c, int prec, int batched, cdag_exec_stats* st) {
       D.graph_mode = c.use_graphs;
     }
     for (hipGraphExec_t ge : D.seg_exec) HIPC(hipGraphLaunch(ge, D.comp));
+    if (!D.graph_finished) HIPC(launch_finish(kp, D.arena, (char*)D.results, D.comp));
     n_segments = (int64_t)D.seg_exec.size();
     for (int64_t g = 0; g < G; ++g) n_launch += kp.launch_off[g + 1] - kp.launch_off[g];
   } else {
@@ -1155,7 +1213,7 @@ void device_execute_static(Ctx& c, int prec, cdag_exec_stats* st) {
   HIPC(hipMemcpyAsync(base + kp.blob_off, kp.blob.data(), kp.blob.size(), hipMemcpyHostToDevice, s));
   if (c.leaves_resident)
     for (int64_t u = 0; u < c.dag.n_leaves; ++u) ops.upload_leaf(u, p.leaf_off[u]);
-  const int64_t G = (int64_t)p.steps.size();
+  const int64_t G = p.n_xsteps();
   int64_t n_launch = walk_steps(c, 0, G, true, false, ops);
   HIPC(launch_finish(kp, base, nullptr, s));
   ++n_launch;

@@ -451,3 +451,51 @@ def test_full_configurations_in_passes_have_no_races(name, prec, policy, chunks,
     assert p["peak_resident"] <= budget
     assert races_by_segment(t) == 0
     assert provenance_errors(t) == []
+
+
+def _staged_case():
+    # six baryons of 16.8 MB: a step uploads more than two 32 MB stages
+    return W.baryon_mix(n_bar=6, n_mes=4, nvec=64, nt=4, n_graphs=24, seed=36, with_data=False)
+
+
+@pytest.mark.parametrize("look", [0, 16, B.LOOKAHEAD_ALL])
+@pytest.mark.parametrize("chunks,resident,mode,wave_max", [(1, False, 0, 4096), (1, True, 1, 4096), (2, False, 0, 4096),
+                                                           (2, False, 2, 4096), (1, False, 1, 3)])
+def test_execution_steps_keep_every_dependency(look, chunks, resident, mode, wave_max):
+    """Batched plans without evictions are issued by their dependencies, across
+    plan steps: no race, every read finds its tensor, each contraction runs once
+    per pass and each transfer is the plan's, no execution step holds more than
+    wave_max contractions, and with little lookahead there are fewer of them
+    than plan steps.  Uploads larger than a stage are spread over several
+    execution steps where they run beside kernels (mode 0)."""
+    for name, wl in _chunk_cases_small() + [("staged", _staged_case())]:
+        c = _ctx(wl)
+        c.schedule("tree")
+        c.set_time_chunks(chunks)
+        c.set_options(leaves_resident=resident, wave_lookahead=look, wave_max=wave_max, use_graphs=mode)
+        p = c.plan("fp64", True)
+        t = c.trace_execute("fp64", True)
+        c.close()
+        assert p["n_evict"] == 0
+        assert races_by_segment(t) == 0
+        assert provenance_errors([r for r in t if not (resident and r["op"] == "read" and r["node"] < len(wl.leaves))]) == []
+        moves = sorted((r["node"], r["step"]) for r in t if r["op"] == "write" and r["stream"] == 1)
+        assert len(moves) == p["n_h2d"] and len(set(moves)) == len(moves)
+        writes = [r["node"] for r in t if r["op"] == "write" and r["stream"] == 0]
+        n_out = p["n_contr"] - p["n_roots"]
+        assert len(writes) == chunks * n_out and len(set(writes)) == n_out
+        per_step = {}
+        for r in t:
+            if r["op"] == "read" and r["stream"] == 0:
+                per_step[r["step"]] = per_step.get(r["step"], 0) + 1
+        assert max(per_step.values()) <= 2 * wave_max
+        if look == 0 and wave_max > 3 and name != "staged":
+            assert len(per_step) < p["n_steps"]
+        if name == "staged" and mode == 0 and not resident and chunks == 1:
+            uploads = {r["event"] for r in t if r["op"] == "record" and r["stream"] == 1}
+            assert len(uploads) >= 3
+
+
+def _chunk_cases_small():
+    return [("meson", W.meson_ring(n_leaves=8, nvec=8, nt=4, n_graphs=40, lmin=4, lmax=7, seed=37, with_data=False)),
+            ("baryon", W.baryon_mix(n_bar=4, n_mes=4, nvec=4, nt=8, n_graphs=30, seed=38, with_data=False))]

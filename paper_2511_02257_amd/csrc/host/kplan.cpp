@@ -376,7 +376,7 @@ KernelPlan make_kernel_plan(const Dag& d, const Plan& p, int prec, const TileTab
           e.nt = h.nt;
           e.splits = h.splits;
           e.item_begin = (int32_t)rd.red_items;
-          rd.red_items += (2LL * e.nt * e.mn + 255) / 256;
+          rd.red_items += red_items(e.nt, e.mn);
           rd.red.push_back(e);
           rd.red_bytes += 2.0 * e.nt * (double)e.mn * ((double)e.splits * acc_bytes + elem_bytes_of(prec));
           rd.red_kinds |= 1 << d.kind[u];

@@ -19,7 +19,7 @@ struct Launch {
   int32_t tile;       // HEC: kernel variant (tile shape and grid policy)
   int32_t n_desc;
   int64_t desc_off;   // arena offset of the first descriptor
-  int64_t n_items;    // HEC: tiles; RED: 256-element blocks; HCA: (root, t) pairs; XSUM: (correlator, t) pairs
+  int64_t n_items;    // HEC: tiles; RED: kRedBlock-element blocks; HCA: (root, t) pairs; XSUM: (correlator, t) pairs
   int64_t host_desc;  // byte offset of the first descriptor in KernelPlan::blob
   double flops = 0;   // algorithmic flops of the launch (HEC, HCA)
   double bytes = 0;   // HEC, HCA: algorithmic bytes; RED: workspace read + output write

@@ -84,8 +84,10 @@ struct IndexMap {
 // Fixed-order reduction of split-K partials into C (one per split op).
 struct RedDesc {
   int64_t ws_off, c_off;
-  int32_t mn, nt, splits, item_begin;          // items: ceil(2*nt*mn / 256) blocks
+  int32_t mn, nt, splits, item_begin;          // items: blocks of kRedBlock of the 2*nt*mn elements
 };
+constexpr int kRedBlock = 1024;
+constexpr int64_t red_items(int64_t nt, int64_t mn) { return (2 * nt * mn + kRedBlock - 1) / kRedBlock; }
 
 // Root trace C(t) = sum_ij P[t,i,j] Q[t,j,i] into the FP64 correlator buffer.
 struct HcaDesc {

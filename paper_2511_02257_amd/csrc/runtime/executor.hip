@@ -842,7 +842,7 @@ int64_t device_autotune(Ctx& c, int prec, int batched, int reps, bool uniform) {
         h.ws_off = h.splits > 1 ? ws : -1;
         h.tile_begin = 0;
         RedDesc r{ws, cc, h.M * h.N, (int32_t)nt, h.splits, 0};
-        const int64_t red_items = (2LL * nt * h.M * h.N + 255) / 256;
+        const int64_t n_red = red_items(nt, (int64_t)h.M * h.N);
         HIPC(hipMemsetAsync(D.arena + a, 0, (size_t)(ws - a), D.comp));
         HIPC(hipMemcpyAsync(D.arena + desc, &h, sizeof(h), hipMemcpyHostToDevice, D.comp));
         HIPC(hipMemcpyAsync(D.arena + desc + 128, &r, sizeof(r), hipMemcpyHostToDevice, D.comp));
@@ -851,7 +851,7 @@ int64_t device_autotune(Ctx& c, int prec, int batched, int reps, bool uniform) {
             hec_interior(h, kTileShapes[variant_tile(v)].bm, kTileShapes[variant_tile(v)].bn, k_step(prec));
         auto once = [&] {
           HIPC(launch_hec(prec, v, interior, D.arena, desc, 1, h.tile_count, D.comp));
-          if (h.splits > 1) HIPC(launch_reduce(prec, D.arena, desc + 128, 1, red_items, D.comp));
+          if (h.splits > 1) HIPC(launch_reduce(prec, D.arena, desc + 128, 1, n_red, D.comp));
         };
         once();
         HIPC(hipEventRecord(e0, D.comp));

@@ -48,6 +48,15 @@ constexpr int64_t trace_blocks(int nth, int64_t n) {
   return (n + traces_per_block(nth) - 1) / traces_per_block(nth);
 }
 
+// The descriptors of a launch: how many, and how many of them one work item
+// is (n / items; exact enough to find an item's descriptor where they all have
+// equally many items).
+struct Span {
+  int32_t n;
+  float per_item;
+};
+inline Span span(int32_t n, int64_t items) { return {n, items > 0 ? (float)n / (float)items : 0.0f}; }
+
 // One exterior contraction inside a grouped launch.
 struct HecDesc {
   int64_t a_off, b_off, c_off;   // t = 0 slice of A, B and C

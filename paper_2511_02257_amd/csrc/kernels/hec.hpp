@@ -108,17 +108,43 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
+// Items of a descriptor.
+__device__ __forceinline__ int32_t item_count(const HecDesc& h) { return h.tile_count; }
+__device__ __forceinline__ int32_t item_count(const HcaDesc& h) { return h.nt; }
+__device__ __forceinline__ int32_t item_count(const RedDesc& h) { return (int32_t)red_items(h.nt, h.mn); }
+__device__ __forceinline__ const int32_t& first_item(const HecDesc& h) { return h.tile_begin; }
+__device__ __forceinline__ const int32_t& first_item(const HcaDesc& h) { return h.item_begin; }
+__device__ __forceinline__ const int32_t& first_item(const RedDesc& h) { return h.item_begin; }
+
+// Descriptor of work item `item`.  The item's share of the launch names it
+// directly where all descriptors have equally many items (one kind and size of
+// contraction, the traces of one time extent) and often where they do not; the
+// descriptor itself says whether it holds the item, and only if it does not is
+// it searched for.  The search reads one word from each of up to 64
+// descriptors, twice from 65 of them on: as many cache lines as an item of
+// N = 48 has operands, and two memory latencies ahead of the item's first
+// load.  With it for every item: N = 45 FP64 rings 811 us, N = 48 FP32 rings
+// 1.32 ms, N = 64 FP64 rings 6.22, in 16 passes 9.18; with the guess 764, 1.26,
+// 5.99, 8.82; mixed launches 19.05 and 19.03, chains 3.10 and 3.06.
+template <typename D>
+__device__ __forceinline__ const D* desc_of(const D* descs, Span n, int64_t item) {
+  const int32_t it = __builtin_amdgcn_readfirstlane((int32_t)item);
+  const D* h = &descs[min((int)(((float)it + 0.5f) * n.per_item), n.n - 1)];
+  const int32_t rel = it - first_item(*h);
+  if (rel >= 0 && rel < item_count(*h)) return h;
+  return &descs[find_desc(&first_item(descs[0]), sizeof(D) / 4, n.n, it)];
+}
+
 struct WorkItem {
   const HecDesc* h;
   int t, m0, n0, sp, kbeg, kend;
 };
 
 template <int BM, int BN>
-__device__ __forceinline__ WorkItem decode_item(const HecDesc* descs, int n_desc, int64_t item) {
+__device__ __forceinline__ WorkItem decode_item(const HecDesc* descs, Span n_desc, int64_t item) {
   WorkItem w;
-  const int di = find_desc(&descs[0].tile_begin, sizeof(HecDesc) / 4, n_desc, item);
-  const HecDesc* h = &descs[di];
-  int64_t local = item - h->tile_begin;
+  const HecDesc* h = desc_of(descs, n_desc, item);
+  uint32_t local = (uint32_t)(item - h->tile_begin);
   // XCD-aware order.  Workgroups go to the eight XCDs round robin (item mod 8
   // for one workgroup per item, and for a persistent grid of a multiple of 8
   // workgroups).  When the contraction's items start on a multiple of 8 and Nt
@@ -126,20 +152,25 @@ __device__ __forceinline__ WorkItem decode_item(const HecDesc* descs, int n_desc
   // per slice): every tile of a slice runs on one XCD, one after another, so
   // the operand panels they share come from that XCD's L2, and each XCD reads
   // only its own slices.  A bijection of the contraction's items; with T = 1
-  // it is the identity.
-  const int64_t T = (int64_t)h->splits * h->tiles_n * h->tiles_m;
-  if (T > 1 && ((h->tile_begin | h->nt) & 7) == 0) {
-    const int32_t x = (int32_t)(local & 7), j = (int32_t)(local >> 3), T32 = (int32_t)T;
-    local = (int64_t)(x + 8 * (j / T32)) * T + (j % T32);
+  // it is the identity.  (T = 1, contractions of one tile: no division at all.)
+  const uint32_t T = h->splits * h->tiles_n * h->tiles_m;   // T nt = tile_count
+  uint32_t tn = 0, tm = 0;
+  w.sp = 0;
+  if (T > 1) {
+    if (((h->tile_begin | h->nt) & 7) == 0) {
+      const uint32_t x = local & 7, j = local >> 3;
+      local = (x + 8 * (j / T)) * T + (j % T);
+    }
+    w.sp = (int)(local % (uint32_t)h->splits);
+    local /= (uint32_t)h->splits;
+    tn = local % (uint32_t)h->tiles_n;
+    local /= (uint32_t)h->tiles_n;
+    tm = local % (uint32_t)h->tiles_m;
+    local /= (uint32_t)h->tiles_m;
   }
-  w.sp = (int)(local % h->splits);
-  local /= h->splits;
-  const int tn = (int)(local % h->tiles_n);
-  local /= h->tiles_n;
-  const int tm = (int)(local % h->tiles_m);
-  w.t = (int)(local / h->tiles_m);
-  w.m0 = tm * BM;
-  w.n0 = tn * BN;
+  w.t = (int)local;
+  w.m0 = (int)tm * BM;
+  w.n0 = (int)tn * BN;
   w.kbeg = w.sp * h->k_split;
   w.kend = min(h->K, w.kbeg + h->k_split);
   w.h = h;
@@ -158,7 +189,8 @@ struct ItemView {
 };
 
 template <typename T, int BM, int BN>
-__device__ __forceinline__ ItemView<T> view_item(char* arena, const HecDesc* descs, int n_desc, int64_t item) {
+__device__ __forceinline__ ItemView<T> view_item(char* arena, const HecDesc* descs, Span n_desc,
+                                                 int64_t item) {
   const WorkItem w = decode_item<BM, BN>(descs, n_desc, item);
   ItemView<T> v;
   v.h = w.h;
@@ -349,8 +381,8 @@ struct TraceItem {
   const T *P, *Q;
   int n, t;
   double* out;
-  __device__ __forceinline__ TraceItem(char* arena, const HcaDesc* descs, int n_desc, int64_t item) {
-    const HcaDesc& h = descs[find_desc(&descs[0].item_begin, sizeof(HcaDesc) / 4, n_desc, item)];
+  __device__ __forceinline__ TraceItem(char* arena, const HcaDesc* descs, Span n_desc, int64_t item) {
+    const HcaDesc& h = *desc_of(descs, n_desc, item);
     t = (int)(item - h.item_begin);
     n = h.n;
     const int64_t nn = (int64_t)n * n;
@@ -377,7 +409,7 @@ struct TraceItem {
 // Wave layout: one trace per wave, lane l keeping the sums l, l + 64, l + 128,
 // l + 192.  No barrier.
 template <typename T, int RPB>
-__device__ __forceinline__ void trace_wave(char* arena, const HcaDesc* descs, int n_desc, int64_t item) {
+__device__ __forceinline__ void trace_wave(char* arena, const HcaDesc* descs, Span n_desc, int64_t item) {
   const TraceItem<T> it(arena, descs, n_desc, item);
   double sr[4], si[4];
   it.template sums<4, RPB>(threadIdx.x & 63, sr, si);
@@ -393,8 +425,8 @@ __device__ __forceinline__ void trace_wave(char* arena, const HcaDesc* descs, in
 // thread of the workgroup calls it equally often; a group with active = false
 // takes part in the barriers only.
 template <typename T, int RPB>
-__device__ __forceinline__ void trace_group(char* arena, const HcaDesc* descs, int n_desc, int64_t item, bool active,
-                                            int g_tid, double (&part)[2][4]) {
+__device__ __forceinline__ void trace_group(char* arena, const HcaDesc* descs, Span n_desc, int64_t item,
+                                            bool active, int g_tid, double (&part)[2][4]) {
   const int wave = g_tid >> 6;
   double sr[1] = {0.0}, si[1] = {0.0};
   double* out = nullptr;
@@ -422,7 +454,7 @@ __device__ __forceinline__ void trace_group(char* arena, const HcaDesc* descs, i
 // layout where the waves are no whole groups of four; blocks load in halves, so
 // that the trace path needs no more registers than the contractions do.
 template <typename T, int NTH>
-__device__ __forceinline__ void trace_block(char* arena, const HcaDesc* descs, int n_desc, int64_t n_items,
+__device__ __forceinline__ void trace_block(char* arena, const HcaDesc* descs, Span n_desc, int64_t n_items,
                                             int64_t b) {
   constexpr int G = traces_per_block(NTH);
   if constexpr (NTH % 256 == 0) {
@@ -475,8 +507,8 @@ __device__ __forceinline__ void store_block(T* C, int M, int N, int row0, int co
 // the last three arguments are unused.
 template <typename T, class TL, int ST, bool PF, bool FULL = false, bool TR = false>
 __global__ void __launch_bounds__(TL::NTH, (occupancy_waves<sizeof(T) == 8 ? 0 : 1, TL, ST, PF, !FULL>()))
-hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc, int64_t n_items,
-         const HcaDesc* __restrict__ tdescs, int n_tdesc, int64_t n_titems) {
+hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, Span n_desc, int64_t n_items,
+         const HcaDesc* __restrict__ tdescs, Span n_tdesc, int64_t n_titems) {
   static_assert(!(TR && PF), "traces ride only in launches of one workgroup per item");
   typedef typename Mfma<T>::V V;
   constexpr int NTH = TL::NTH, BM = TL::BM, BN = TL::BN, TM = TL::TM, TN = TL::TN;
@@ -874,8 +906,8 @@ template <int P> __device__ constexpr int term_y(int t) {
 // TR as in hec_mfma (the traces read the FP32 storage of these modes).
 template <class TL, int ST_, bool PF, int P, bool FULL = false, bool TR = false>
 __global__ void __launch_bounds__(TL::NTH, (Occupancy<2, TL, ST_, PF>::waves))
-hec_bf16(char* __restrict__ arena, const HecDesc* __restrict__ descs, int n_desc, int64_t n_items,
-         const HcaDesc* __restrict__ tdescs, int n_tdesc, int64_t n_titems) {
+hec_bf16(char* __restrict__ arena, const HecDesc* __restrict__ descs, Span n_desc, int64_t n_items,
+         const HcaDesc* __restrict__ tdescs, Span n_tdesc, int64_t n_titems) {
   static_assert(!(TR && PF), "traces ride only in launches of one workgroup per item");
   constexpr int NTH = TL::NTH, BM = TL::BM, BN = TL::BN, TM = TL::TM, TN = TL::TN;
   constexpr int BK = 32, PAD = BK + 8;     // bf16 per LDS row (16-byte aligned rows)

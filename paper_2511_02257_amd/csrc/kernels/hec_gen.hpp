@@ -38,7 +38,7 @@ __device__ __forceinline__ int64_t digit_offset(uint32_t x, int nd, uint32_t n, 
 // 0.57 -> 0.14 ms.
 template <typename T>
 __global__ void __launch_bounds__(256) hec_general(char* __restrict__ arena, const HecDesc* __restrict__ descs,
-                                                   int n_desc, int64_t n_items, const HcaDesc*, int, int64_t) {
+                                                   Span n_desc, int64_t n_items, const HcaDesc*, Span, int64_t) {
   typedef typename Mfma<T>::V V;
   constexpr int B = 32, BK = 32, PAD = BK + 1, KT = 256;
   constexpr int E = 2 * B * BK / 256;   // elements of A, and of B, per thread and slice

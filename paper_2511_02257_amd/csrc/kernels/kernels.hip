@@ -21,13 +21,12 @@ namespace cdag {
 // (3.5 TB/s), this form 0.21 (5.7 TB/s).
 template <typename T>
 __global__ void __launch_bounds__(256) splitk_reduce(char* __restrict__ arena, const RedDesc* __restrict__ descs,
-                                                     int n_desc, int64_t n_items) {
+                                                     Span n_desc, int64_t n_items) {
   constexpr int W = 16 / (int)sizeof(T), PER = kRedBlock / 256;   // elements per vector, per thread
   typedef T VT __attribute__((ext_vector_type(W)));
   typedef VT VU __attribute__((aligned(sizeof(T))));              // slices of odd length
   for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
-    const int di = find_desc(&descs[0].item_begin, sizeof(RedDesc) / 4, n_desc, item);
-    const RedDesc& r = descs[di];
+    const RedDesc& r = *desc_of(descs, n_desc, item);
     const int64_t total = 2LL * r.nt * r.mn;
     const T* ws = reinterpret_cast<const T*>(arena + r.ws_off);
     T* out = reinterpret_cast<T*>(arena + r.c_off);
@@ -68,7 +67,7 @@ __global__ void __launch_bounds__(256) splitk_reduce(char* __restrict__ arena, c
 // would spread over few compute units with several rounds of loads per wave.
 template <typename T, bool WG>
 __global__ void __launch_bounds__(256, 3) hca_trace(char* __restrict__ arena, const HcaDesc* __restrict__ descs,
-                                                    int n_desc, int64_t n_items) {
+                                                    Span n_desc, int64_t n_items) {
   if constexpr (WG) {
     __shared__ double part[2][4];
     for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x)
@@ -101,13 +100,13 @@ __global__ void __launch_bounds__(256, 3) hca_trace(char* __restrict__ arena, co
 // gap before it; this form, the copy included, takes 2.3 and 22 us (1 MB at
 // 45 GB/s).
 __global__ void __launch_bounds__(256) xsum_kernel(char* __restrict__ arena, const XsumDesc* __restrict__ descs,
-                                                   const XsumEntry* __restrict__ entries, int n_desc, int64_t n_items,
+                                                   const XsumEntry* __restrict__ entries, Span n_desc, int64_t n_items,
                                                    int64_t corr_off, int64_t corr_bytes, char* __restrict__ host) {
   typedef double v2d __attribute__((ext_vector_type(2)));
   __shared__ double red[2][128];
   const int tid = threadIdx.x;
   for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
-    const XsumDesc& x = descs[find_desc(&descs[0].item_begin, sizeof(XsumDesc) / 4, n_desc, item)];
+    const XsumDesc& x = descs[find_desc(&descs[0].item_begin, sizeof(XsumDesc) / 4, n_desc.n, item)];
     const int t = (int)(item - x.item_begin);
     double sr = 0.0, si = 0.0;
     for (int e = x.e_begin + tid; e < x.e_end; e += 256) {
@@ -250,7 +249,7 @@ unsigned grid_for(int64_t items) { return (unsigned)std::max<int64_t>(1, std::mi
 void set_args(KernelCall& k, char* arena, const void* desc, int n_desc, int64_t n_items) {
   k.arena = arena;
   k.desc = desc;
-  k.n_desc = n_desc;
+  k.n_desc = span(n_desc, n_items);
   k.n_items = n_items;
 }
 }  // namespace
@@ -310,12 +309,12 @@ hipError_t hec_call(int prec, int variant, bool interior, char* arena, int64_t d
     if (blocks > kMaxGrid) return hipErrorInvalidValue;
     k->grid = (unsigned)blocks;
     k->tdesc = arena + tdesc_off;
-    k->n_tdesc = n_tdesc;
+    k->n_tdesc = span(n_tdesc, n_titems);
     k->n_titems = n_titems;
   } else {
     k->grid = persistent ? persistent_grid(fn, k->block, n_items) : grid_for(n_items);
     k->tdesc = nullptr;
-    k->n_tdesc = 0;
+    k->n_tdesc = span(0, 0);
     k->n_titems = 0;
   }
   return hipSuccess;

@@ -20,10 +20,10 @@ struct KernelCall {
   char* arena = nullptr;
   const void* desc = nullptr;
   const void* entries = nullptr;
-  int n_desc = 0;
+  Span n_desc{};
   int64_t n_items = 0;
   const void* tdesc = nullptr;
-  int n_tdesc = 0;
+  Span n_tdesc{};
   int64_t n_titems = 0;
   int64_t corr_off = 0, corr_bytes = 0;
   char* host = nullptr;

@@ -813,6 +813,27 @@ def test_general_kernel_sizes(prec, nvec, nt):
     assert err <= TOL[prec]
 
 
+@pytest.mark.parametrize("case", ["rings_nt1", "rings_nt7", "rings_tiles", "mixed"])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_descriptor_of_an_item(prec, case):
+    """Launches whose descriptors hold equally many items (one each, a few,
+    several tiles a slice; more descriptors than one search round reads) and
+    launches of contractions, reductions and traces of different counts, against
+    the oracle."""
+    if case == "mixed":
+        wl = W.baryon_mix(n_mes=8, n_bar=6, nvec=24, nt=3, n_graphs=40, sigma=24 ** -0.5, n_corr=3, seed=74)
+    else:
+        nvec, nt, graphs = {"rings_nt1": (8, 1, 300), "rings_nt7": (12, 7, 120), "rings_tiles": (72, 2, 40)}[case]
+        wl = W.meson_ring(n_leaves=24, nvec=nvec, nt=nt, n_graphs=graphs, lmin=3, lmax=6, sigma=nvec ** -0.5, n_corr=3,
+                          seed=74)
+    ref = OV.correlators(wl)
+    a = run(wl, "tree", prec, True)
+    want, got = np.concatenate([ref[g] for g in ref]), np.concatenate([a["corr"][g] for g in ref])
+    err = np.linalg.norm(got - want) / np.linalg.norm(want)
+    print(f"{case} {prec}: rel {err:.3e}")
+    assert err <= TOL[prec]
+
+
 @pytest.mark.parametrize("nvec,nt,chunks,n_leaves", [(3, 1, 1, 40), (9, 6, 3, 6), (64, 4, 2, 6), (24, 8, 1, 34)])
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_grouped_transfers(prec, nvec, nt, chunks, n_leaves):

@@ -539,12 +539,14 @@ hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, Span n_des
   T (&Bs)[ST][2][BK][BPAD] = *reinterpret_cast<T (*)[ST][2][BK][BPAD]>(smem + A_ELEMS);  // [stage][plane][k][n]
   T (&Cs)[2][BM][CPAD] = *reinterpret_cast<T (*)[2][BM][CPAD]>(smem);                   // [plane][m][n]
   // RAG: a ragged launch.  A wave skips the 16 x 16 blocks that lie outside
-  // M x N and the 4-deep k steps past the k range; the waves' places in the
-  // tile turn with the workgroup, so that the places with fewer blocks fall on
-  // every SIMD alike.
+  // M x N and the 4-deep k steps past the k range.  The waves keep their places
+  // in every workgroup: the dispatcher itself starts a compute unit's next
+  // workgroup on another SIMD, so that the places with fewer blocks fall on all
+  // alike (N = 48 FP32 rings 1.32 ms; with the places turned by the
+  // workgroup's turn on its compute unit 1.48).
   constexpr bool RAG = !FULL;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(RAG ? ((tid >> 6) + (int)blockIdx.x) % (NTH / 64) : tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / TL::WGN, wn = wave % TL::WGN, li = lane & 15, lk = lane >> 4;
 
   typedef typename Vec16<T>::V VL;
@@ -925,8 +927,7 @@ hec_bf16(char* __restrict__ arena, const HecDesc* __restrict__ descs, Span n_des
   __shared__ __attribute__((aligned(16))) __bf16 As[ST][2][P][BM][PAD];
   __shared__ __attribute__((aligned(16))) __bf16 Bs[ST][2][P][BN][PAD];
   const int tid = threadIdx.x, lane = tid & 63;
-  // ragged launches turn the waves' places as in hec_mfma
-  const int wave = __builtin_amdgcn_readfirstlane(FULL ? tid >> 6 : ((tid >> 6) + (int)blockIdx.x) % (NTH / 64));
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / TL::WGN, wn = wave % TL::WGN, li = lane & 15, lk = lane >> 4;
 
   // loaded operands as whole register tuples (see Vec16)

@@ -135,7 +135,11 @@ static void retile(int v, HecDesc* h) {
 // Measured (us, waves of one kind, Nt 8 to 32; N and M: the GEMM's):
 //   three products (N <= 32): 32 x 32, but 64 x 32 from M = 64 on (K32 at N =
 //     32: FP64 119 -> 102, FP32 68 -> 59; K22, M = 32: 130 against 184);
-//   four products: 64 x 64, or 48 x 48 where N fills its tiles better (FP64 K33
+//   four products: from N = 65 to 80, for short K, 64 x 80 with no padded
+//     column of blocks (K32 at N = 72 FP64 2148 -> 1487, FP32 1144 -> 803, at 66
+//     1740 -> 1224 and 952 -> 685; K22 at 72 1991 -> 1714 and 1086 -> 929; but
+//     K33, whose M = N = 72 are two of its tiles, 2400 against 2972);
+//     otherwise 64 x 64, or 48 x 48 where N fills its tiles better (FP64 K33
 //     at N = 72 2860 -> 2338, 96 7533 -> 5134, FP32 K22 at 96 1563 -> 1180; at
 //     64 964 against 1389), to N = 64 only for long K (FP64 K33 at N = 48
 //     450 -> 368; K22, K = N: FP32 at 48 240 against 279, FP64 at 45 540
@@ -152,6 +156,7 @@ int default_variant(int prec, int variant, const Gemm& g) {
     if (g.N <= 64) return variant_of(0, 1, 1);
     return prec == 2 ? variant_of(3, 1, 1) : kExtraVariantId;
   }
+  if (g.N > 64 && g.N <= 80 && g.K < 512) return kExtraVariantId + kNumTiles;
   const bool fits48 = (g.N + 47) / 48 * 48 < (g.N + 63) / 64 * 64;
   return variant_of(fits48 && (g.N > 64 || g.K >= 512) ? 2 : 0, 1, 1);
 }

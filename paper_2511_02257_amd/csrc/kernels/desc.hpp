@@ -17,17 +17,17 @@ namespace cdag {
 
 // Exterior-contraction tile shapes (workgroup output tile BM x BN, threads).
 // The kernels instantiate exactly these, in this order.  The first kNumTiles
-// can be chosen (cdag_set_tile); the last runs only where no choice was made,
-// in split BF16.
+// can be chosen (cdag_set_tile); the others run only where no choice was made,
+// the first of them in split BF16, the second in FP64 and FP32.
 struct TileShape { int32_t bm, bn, nth; };
-constexpr int kNumTiles = 6, kAllTiles = 7;
+constexpr int kNumTiles = 6, kAllTiles = 8;
 constexpr TileShape kTileShapes[kAllTiles] = {{64, 64, 256}, {32, 32, 256}, {48, 48, 64},   {128, 64, 256},
-                                              {64, 32, 256}, {64, 64, 512}, {128, 128, 512}};
+                                              {64, 32, 256}, {64, 64, 512}, {128, 128, 512}, {64, 80, 256}};
 
 // Launch variant: tile + kNumTiles * (grid + 2 * (2 - stages)) for the tiles
 // that can be chosen, then the general kernel (contractions over any index
 // pairs), then kExtraVariantId + kNumTiles * (tile - kNumTiles) for the other
-// tile (one LDS stage, one workgroup per item).
+// tiles (one LDS stage, one workgroup per item).
 constexpr int kGenVariantId = 4 * kNumTiles;
 constexpr int kExtraVariantId = 5 * kNumTiles;
 constexpr int variant_tile(int v) {

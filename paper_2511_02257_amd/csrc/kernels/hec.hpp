@@ -61,6 +61,11 @@ typedef Tile<2, 2, 2, 1> Tile4;   //  64 x 32, 256 threads
 typedef Tile<2, 4, 2, 1> Tile5;   //  64 x 64, 512 threads (half the accumulators per wave)
 // Split BF16 without a choice only: one LDS stage, one workgroup per item.
 typedef Tile<2, 4, 4, 2> Tile6;   // 128 x 128, 512 threads
+// FP64 and FP32 without a choice only, likewise: five blocks a wave, so that N
+// = 65 .. 80 takes one tile across with every wave equally busy (it ran 48 x 48
+// tiles of one wave each before, whose operands no other wave shared: FP64 K32
+// at N = 72 30 TFLOP/s, now 43).
+typedef Tile<4, 1, 1, 5> Tile7;   //  64 x 80, 256 threads
 
 // Occupancy target of an exterior-contraction kernel: the waves per SIMD that
 // its register budget must allow (the compiler keeps each lane within
@@ -82,6 +87,8 @@ CDAG_OCCUPANCY(0, Tile0, 2, 2)
 CDAG_OCCUPANCY(0, Tile4, 1, 3)
 CDAG_OCCUPANCY(0, Tile4, 2, 2)
 CDAG_OCCUPANCY(0, Tile1, 1, 4)
+CDAG_OCCUPANCY(0, Tile7, 1, 2)
+CDAG_OCCUPANCY(1, Tile7, 1, 3)
 CDAG_OCCUPANCY(1, Tile0, 1, 4)
 CDAG_OCCUPANCY(1, Tile0, 2, 4)
 CDAG_OCCUPANCY(1, Tile3, 1, 3)
@@ -515,7 +522,9 @@ hec_mfma(char* __restrict__ arena, const HecDesc* __restrict__ descs, Span n_des
   // k-slice: 16 (FP64) or 32 (FP32) k per LDS stage, so that a K = 64
   // contraction's item runs four or two slices.  A rows are padded so that
   // the 16 rows read by one instruction fall in distinct LDS banks.
-  constexpr int BK = sizeof(T) == 8 ? 16 : 32, APAD = BK + (sizeof(T) == 8 ? 1 : 4), BPAD = BN + 16;
+  constexpr int BK = sizeof(T) == 8 ? 16 : 32, APAD = BK + (sizeof(T) == 8 ? 1 : 4);
+  // the four k rows that one instruction reads of B start 16 (or 48) banks apart
+  constexpr int BPAD = BN == 80 ? BN : BN + 16;
   constexpr int SPR = BK / 8;   // 8-element A segments per row
   // The A tile is split into 8-element row segments ([plane][row][k / 8]); the
   // B tile into 16-byte row chunks of W elements ([plane][k][n / W]), so that
@@ -1186,6 +1195,7 @@ static_assert(Tile3::BM == kTileShapes[3].bm && Tile3::BN == kTileShapes[3].bn &
 static_assert(Tile4::BM == kTileShapes[4].bm && Tile4::BN == kTileShapes[4].bn && Tile4::NTH == kTileShapes[4].nth, "tile 4");
 static_assert(Tile5::BM == kTileShapes[5].bm && Tile5::BN == kTileShapes[5].bn && Tile5::NTH == kTileShapes[5].nth, "tile 5");
 static_assert(Tile6::BM == kTileShapes[6].bm && Tile6::BN == kTileShapes[6].bn && Tile6::NTH == kTileShapes[6].nth, "tile 6");
+static_assert(Tile7::BM == kTileShapes[7].bm && Tile7::BN == kTileShapes[7].bn && Tile7::NTH == kTileShapes[7].nth, "tile 7");
 
 // Kernel of one launch variant in a per-precision table: K<TL, ST, PF, IN, TR>::fn()
 // is the kernel for tile TL, ST LDS stages, persistent grid PF, interior
@@ -1205,8 +1215,8 @@ const void* hec_pick(int stages, bool persistent, bool interior, bool traces) {
   return stages == 2 ? hec_pick_st<K, TL, 2>(persistent, interior, traces)
                      : hec_pick_st<K, TL, 1>(persistent, interior, traces);
 }
-// WIDE: the precision has kernels of tile 6.
-template <template <class, int, bool, bool, bool> class K, bool WIDE>
+// X, TX: the tile besides the choices that the precision has kernels of.
+template <template <class, int, bool, bool, bool> class K, int X, class TX>
 const void* hec_table(int tile, int stages, bool persistent, bool interior, bool traces) {
   switch (tile) {
     case 0: return hec_pick<K, Tile0>(stages, persistent, interior, traces);
@@ -1215,13 +1225,10 @@ const void* hec_table(int tile, int stages, bool persistent, bool interior, bool
     case 3: return hec_pick<K, Tile3>(stages, persistent, interior, traces);
     case 4: return hec_pick<K, Tile4>(stages, persistent, interior, traces);
     case 5: return hec_pick<K, Tile5>(stages, persistent, interior, traces);
-    case 6:
-      if constexpr (WIDE) {
-        if (stages != 1 || persistent) return nullptr;
-        if (traces) return interior ? K<Tile6, 1, false, true, true>::fn() : K<Tile6, 1, false, false, true>::fn();
-        return interior ? K<Tile6, 1, false, true, false>::fn() : K<Tile6, 1, false, false, false>::fn();
-      }
-      return nullptr;
+    case X:
+      if (stages != 1 || persistent) return nullptr;
+      if (traces) return interior ? K<TX, 1, false, true, true>::fn() : K<TX, 1, false, false, true>::fn();
+      return interior ? K<TX, 1, false, true, false>::fn() : K<TX, 1, false, false, false>::fn();
     default: return nullptr;
   }
 }

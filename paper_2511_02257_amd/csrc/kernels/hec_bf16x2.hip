@@ -12,7 +12,7 @@ struct Kern {
 }  // namespace
 
 const void* hec_kernel_bf16x2(int tile, int stages, bool persistent, bool interior, bool traces) {
-  return hec_table<Kern, true>(tile, stages, persistent, interior, traces);
+  return hec_table<Kern, 6, Tile6>(tile, stages, persistent, interior, traces);
 }
 
 }  // namespace cdag

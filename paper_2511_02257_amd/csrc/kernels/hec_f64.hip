@@ -13,7 +13,7 @@ struct Kern {
 }  // namespace
 
 const void* hec_kernel_f64(int tile, int stages, bool persistent, bool interior, bool traces) {
-  return hec_table<Kern, false>(tile, stages, persistent, interior, traces);
+  return hec_table<Kern, 7, Tile7>(tile, stages, persistent, interior, traces);
 }
 
 const void* hec_general_f64() {

@@ -813,6 +813,24 @@ def test_general_kernel_sizes(prec, nvec, nt):
     assert err <= TOL[prec]
 
 
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nvec,nt", [(65, 2), (72, 3), (80, 8)])
+def test_default_tile_65_to_80(prec, nvec, nt):
+    """The 64 x 80 tile at the ends of its range (one column in its last block;
+    every block whole, interior rows included) and between: the oracle, and the
+    bits of the 64 x 64 tile, which runs the same products in the same order."""
+    kw = dict(nvec=nvec, nt=nt, n_corr=2, seed=75)
+    for wl in (W.meson_ring(n_leaves=5, n_graphs=8, lmin=3, lmax=5, name="ring", sigma=nvec ** -0.5, **kw),
+               W.baryon_mix(n_bar=2, n_mes=3, n_graphs=3, name="chain", sigma=1 / nvec, **kw)):
+        ref = OV.correlators(wl)
+        a, b = run(wl, "tree", prec, True), run(wl, "tree", prec, True, tile=0)
+        want, got = np.concatenate([ref[g] for g in ref]), np.concatenate([a["corr"][g] for g in ref])
+        err = np.linalg.norm(got - want) / np.linalg.norm(want)
+        print(f"{wl.name} N={nvec} {prec}: rel {err:.3e}")
+        assert err <= TOL[prec]
+        assert np.array_equal(np.concatenate(a["corr"]).view(np.uint64), np.concatenate(b["corr"]).view(np.uint64))
+
+
 @pytest.mark.parametrize("case", ["rings_nt1", "rings_nt7", "rings_tiles", "mixed"])
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_descriptor_of_an_item(prec, case):

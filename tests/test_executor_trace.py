@@ -496,6 +496,21 @@ def test_execution_steps_keep_every_dependency(look, chunks, resident, mode, wav
             assert len(uploads) >= 3
 
 
+@pytest.mark.parametrize("nvec,regrouped", [(8, True), (96, False)])
+def test_many_long_steps_are_issued_as_planned(nvec, regrouped):
+    """A plan of more than 32 steps of over 100 us of contractions each (N = 96)
+    is issued plan step by plan step; the same graphs with short steps are
+    regrouped into fewer."""
+    c = _ctx(W.baryon_mix(n_bar=12, n_mes=12, nvec=nvec, nt=16, n_graphs=120, seed=39, with_data=False))
+    c.schedule("tree")
+    c.set_options(leaves_resident=True)
+    p = c.plan("fp64", True)
+    steps = {r["step"] for r in c.trace_execute("fp64", True) if r["op"] == "read" and r["stream"] == 0}
+    c.close()
+    assert p["n_steps"] > 32 and p["n_evict"] == 0
+    assert len(steps) < p["n_steps"] if regrouped else len(steps) == p["n_steps"]
+
+
 def _chunk_cases_small():
     return [("meson", W.meson_ring(n_leaves=8, nvec=8, nt=4, n_graphs=40, lmin=4, lmax=7, seed=37, with_data=False)),
             ("baryon", W.baryon_mix(n_bar=4, n_mes=4, nvec=4, nt=8, n_graphs=30, seed=38, with_data=False))]

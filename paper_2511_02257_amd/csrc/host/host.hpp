@@ -169,6 +169,7 @@ struct PlanOpts {
   // Rates by which place() tells whether uploads or contractions bound a pass
   // (flop/s of the precision's kernels, bytes/s of the host link).
   double flop_rate = 65e12, link_rate = 50e9;
+  std::vector<double> item_flops;  // per node: flops of one work item (empty: not known)
 };
 
 // Plan of one pass (t_chunks = 1: the whole execution).  Counters and the

@@ -171,6 +171,39 @@ int default_tile(int prec, int kind, int n) {
   return choice_of(variant_of(tile, 1), true);
 }
 
+// Descriptor (without offsets) of exterior contraction u over nt_run of its time
+// slices; returns the kernel variant that runs it.  The split-K decision is the
+// contraction's own (independent of batching), so results do not depend on how
+// contractions are grouped into launches.
+static int contraction_of(const Dag& d, int64_t u, int prec, const TileTable& tiles, int nt_run, HecDesc* h) {
+  Gemm g;
+  d.gemm_shape(u, &g.M, &g.N, &g.K);
+  *h = HecDesc{};
+  if (is_spec(d.kind[u])) {
+    decompose(g, d.nt[u], choice_of(variant_of(kGenTile, 1, 2), false), prec, h, nt_run);
+    return kGenVariant;
+  }
+  const auto it = tiles.find(std::make_tuple(prec, (int)d.kind[u], (int)d.nvec[u]));
+  const int choice = it != tiles.end() ? it->second : default_tile(prec, d.kind[u], d.nvec[u]);
+  decompose(g, d.nt[u], choice, prec, h, nt_run);
+  if (it != tiles.end()) return choice_variant(choice);
+  const int v = default_variant(prec, choice_variant(choice), g);
+  retile(v, h);
+  return v;
+}
+
+std::vector<double> item_flops(const Dag& d, int prec, const TileTable& tiles) {
+  std::vector<double> out(d.n_nodes(), 0.0);
+  for (int64_t u = d.n_leaves; u < d.n_nodes(); ++u) {
+    if (d.kind[u] == HCA) continue;
+    HecDesc h;
+    const int v = contraction_of(d, u, prec, tiles, d.nt[u], &h);
+    const TileShape& ts = kTileShapes[v == kGenVariant ? kGenTile : variant_tile(v)];
+    out[u] = 8.0 * std::min(ts.bm, h.M) * std::min(ts.bn, h.N) * h.k_split;
+  }
+  return out;
+}
+
 KernelPlan make_kernel_plan(const Dag& d, const Plan& p, int prec, const TileTable& tiles, bool fuse_traces) {
   KernelPlan kp;
   kp.prec = prec;
@@ -198,13 +231,6 @@ KernelPlan make_kernel_plan(const Dag& d, const Plan& p, int prec, const TileTab
   }
   kp.sums_bytes = align256(std::max<int64_t>(so, 16));
 
-  // split-K decision per contraction (independent of batching, so results do
-  // not depend on how contractions are grouped into launches)
-  auto tile_of = [&](int64_t u) -> int {
-    if (is_spec(d.kind[u])) return choice_of(variant_of(kGenTile, 1, 2), false);
-    auto it = tiles.find(std::make_tuple(prec, (int)d.kind[u], (int)d.nvec[u]));
-    return it != tiles.end() ? it->second : default_tile(prec, d.kind[u], d.nvec[u]);
-  };
   for (int64_t u = d.n_leaves; u < d.n_nodes(); ++u)
     if (is_spec(d.kind[u]) && prec >= 2)
       throw Error(CDAG_E_INVALID, "contractions over any index pairs run in FP64 and FP32 only");
@@ -219,19 +245,7 @@ KernelPlan make_kernel_plan(const Dag& d, const Plan& p, int prec, const TileTab
   std::vector<int> variant(d.n_nodes(), -1);
   for (int64_t u = d.n_leaves; u < d.n_nodes(); ++u) {
     if (d.kind[u] == HCA) continue;
-    Gemm g;
-    d.gemm_shape(u, &g.M, &g.N, &g.K);
-    const int choice = tile_of(u);
-    proto[u] = HecDesc{};
-    decompose(g, d.nt[u], choice, prec, &proto[u], (int)(d.nt[u] / p.chunks()));
-    if (is_spec(d.kind[u])) {
-      variant[u] = kGenVariant;
-    } else if (tiles.count(std::make_tuple(prec, (int)d.kind[u], (int)d.nvec[u]))) {
-      variant[u] = choice_variant(choice);
-    } else {
-      variant[u] = default_variant(prec, choice_variant(choice), g);
-      retile(variant[u], &proto[u]);
-    }
+    variant[u] = contraction_of(d, u, prec, tiles, (int)(d.nt[u] / p.chunks()), &proto[u]);
   }
   auto ws_of = [&](const HecDesc& h) {
     return h.splits > 1 ? align256((int64_t)h.splits * h.nt * 2 * h.M * h.N * acc_bytes) : 0;

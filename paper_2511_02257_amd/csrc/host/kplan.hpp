@@ -108,6 +108,8 @@ struct KernelPlan {
   int64_t hec_items = 0;                  // summed over all exterior-contraction launches
 };
 
+// Algorithmic flops of one work item (output tile, K split) of each contraction.
+std::vector<double> item_flops(const Dag& d, int prec, const TileTable& tiles);
 int64_t elem_bytes_of(int prec);                 // 16 for FP64, 8 otherwise
 // Strides of spec s on tensors of dimension n (desc.hpp, IndexMap).
 IndexMap index_map(const Spec& s, int n);

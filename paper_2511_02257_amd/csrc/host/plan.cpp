@@ -298,6 +298,10 @@ constexpr int64_t kStageBytes = 32LL << 20;
 constexpr int64_t kFewSteps = 32;
 constexpr double kLongStep = 100e-6;
 
+// modelled_time(): launch and latency of a step, compute units, and the share of
+// the plan steps' time that another cut has to stay below.
+constexpr double kStepTime = 7e-6, kUnits = 256, kWorthCutting = 0.99;
+
 // How execution steps are cut (place()).
 enum Cut { PLAN_STEPS, STAGED, MERGED };
 
@@ -462,6 +466,39 @@ Plan::Program place_pool(const Dag& d, Plan& p, int64_t base, int64_t cap, Cut c
       if (issued(r) && (r.op == OP_D2H || r.op == OP_H2D) == transfers) g.recs[at[r.xstep]++] = r;
   return g;
 }
+
+// Modelled time of the passes in eager issue: uploads one after another at the
+// link's rate beside the kernels, each after the kernels that last used its
+// memory (a pass after the one two before it), and each step's kernels after its
+// uploads, for as long as its contractions take on the whole chip, or as its
+// longest work item takes on one compute unit, whichever is more.  It is for
+// putting cuts of one plan in order, not for their absolute times.
+double modelled_time(const Dag& d, const Plan& p, const Plan::Program& first, const Plan::Program& later) {
+  double up = 0, comp = 0, pass_end[2] = {0, 0};
+  std::vector<double> done;                  // end of each step's kernels in the pass
+  for (int64_t k = 0; k < p.chunks(); ++k) {
+    const Plan::Program& g = k == 0 ? first : later;
+    done.assign(g.n(), 0.0);
+    up = std::max(up, pass_end[k % 2]);
+    for (int64_t s = 0; s < g.n(); ++s) {
+      double work = 0, item = 0, ready = comp;
+      for (int64_t i = g.off[s]; i < g.off[s + 1]; ++i) {
+        const PlanRec& r = g.recs[i];
+        if (r.op == OP_H2D) {
+          if (r.wait_comp >= 0) up = std::max(up, done[r.wait_comp]);
+          up += (double)p.tsize(d, r.node) / p.opts.link_rate;
+          ready = std::max(ready, up);
+        } else if (r.op == OP_EXEC) {
+          work += d.flops(r.node);
+          if (!p.opts.item_flops.empty()) item = std::max(item, p.opts.item_flops[r.node]);
+        }
+      }
+      done[s] = comp = ready + kStepTime + std::max(work / (double)p.chunks(), item * kUnits) / p.opts.flop_rate;
+    }
+    pass_end[k % 2] = comp;
+  }
+  return comp;
+}
 }  // namespace
 
 // Execution steps.  A plan that runs in waves and never evicts need not be
@@ -481,15 +518,21 @@ Plan::Program place_pool(const Dag& d, Plan& p, int64_t base, int64_t cap, Cut c
 //     execution steps, each with a stage of the uploads and the contractions
 //     whose operands are there by then, so that kernels start before the last
 //     leaf.
-// A plan step with staged uploads: the first pass over the time slices is
-// MERGED, which also moves later plan steps' contractions up between the stages.
-// So are later passes where the uploads take longer than the contractions, as
-// only the work after the last upload then counts (five N families in two
-// passes, 0.88 GB of leaves: 24.0 ms by plan steps, 22.0 with the second pass
-// STAGED, 19.1 MERGED).  Else the uploads of a pass hide behind the pass before,
-// and a launch of few long items (K33) cut into several leaves compute units
-// idle in each (headline in 8 passes: 37.9 ms by plan steps, 44 with every pass
-// MERGED, 36.6 with the later ones STAGED).
+// Where uploads are staged and MERGED does not make fewer steps, every cut adds
+// steps, so it has to hide more of the uploads than they cost: a step takes at
+// least as long as its longest work item (a K33 item with the whole K: 0.5 ms).
+// The passes are modelled (modelled_time()), the first MERGED, which also moves
+// later plan steps' contractions up between the stages, and the later ones as
+// the plan's steps, STAGED or MERGED; the plan's steps stay unless a cut is
+// modelled at least 1 % shorter.  Measured (ms; baryon chains at N = 64, 8
+// passes, FP64, K33 in whole items; by plan steps, then with the later passes
+// as planned, STAGED, MERGED; * what the model takes):
+//   every ready contraction in a wave, 24 plan steps   38.0  36.7  36.0*  44.1
+//   lookahead 64, 184                                  82.6* 82.7  86.1   92.5
+//   Sibling, lookahead 16, 576                        253.6* 253.8 266.3 266.6
+// and five N families in 4 passes, FP32, lookahead 64   35.0  33.1  31.5  30.2*
+// (with the model in FP64 in place of a rule on the pass's upload and
+// contraction times alone: 67.8 -> 62.4).
 // Plans of many long steps keep their plan steps: launches cost them nothing,
 // and a contraction that moves up leaves its output waiting for its consumer
 // long enough to drop out of the last-level cache (20,301 contractions in 1,151
@@ -525,9 +568,20 @@ void place(const Dag& d, Plan& p) {
     if (merged.n() < p.first.n()) {
       p.first = std::move(merged);
     } else if (staged) {
-      p.first = std::move(merged);
-      if ((double)p.h2d_bytes / p.opts.link_rate < t_pass) {
-        p.later = place_pool(d, p, base, 0, STAGED);
+      const Plan::Program cut = place_pool(d, p, base, 0, STAGED);
+      const Plan::Program* later = nullptr;
+      double best = modelled_time(d, p, p.first, p.first) * kWorthCutting;
+      const Plan::Program* const cuts[] = {&p.first, &cut, &merged};
+      for (const Plan::Program* l : cuts) {
+        const double t = modelled_time(d, p, merged, *l);
+        if (t < best) {
+          best = t;
+          later = l;
+        }
+      }
+      if (later != nullptr) {
+        p.later = *later;
+        p.first = std::move(merged);
         return;
       }
     }

@@ -514,3 +514,27 @@ def test_many_long_steps_are_issued_as_planned(nvec, regrouped):
 def _chunk_cases_small():
     return [("meson", W.meson_ring(n_leaves=8, nvec=8, nt=4, n_graphs=40, lmin=4, lmax=7, seed=37, with_data=False)),
             ("baryon", W.baryon_mix(n_bar=4, n_mes=4, nvec=4, nt=8, n_graphs=30, seed=38, with_data=False))]
+
+
+@pytest.mark.parametrize("policy", ["sibling", "node", "tree"])
+def test_long_items_keep_short_steps_as_planned(policy):
+    """The baryon DAG in 8 passes, every K33 a single work item over the whole K:
+    a step takes as long as that item, so with short steps (lookahead 16) no cut
+    of a plan step adds one; with every ready contraction in a wave the passes'
+    uploads are still staged."""
+    wl = W.config("baryon_mix", with_data=False)
+    c = _ctx(wl)
+    c.schedule(policy)
+    c.set_mem_budget(wl.budget_bytes)
+    c.set_time_chunks(8)
+    for kind in (B.K32, B.K33):
+        c.set_tile("fp64", kind, 64, 5, 1, 1, 0)
+    n = {}
+    for look in (16, B.LOOKAHEAD_ALL):
+        c.set_options(wave_lookahead=look, use_graphs=0)
+        p = c.plan("fp64", True)
+        assert p["n_evict"] == 0
+        n[look] = p["n_steps"], len({r["step"] for r in c.trace_execute("fp64", True) if r["op"] == "read" and r["stream"] == 0})
+    c.close()
+    assert n[16][1] == n[16][0]
+    assert n[B.LOOKAHEAD_ALL][1] > n[B.LOOKAHEAD_ALL][0]

@@ -330,7 +330,7 @@ def variant_index(tile: int, grid: int, lds_stages: int) -> int:
 
 
 def cdag_trace_execute(h, prec: str = "fp64", batched: bool = False, fail_at: int = -1) -> List[dict]:
-    """The eager two-stream issue order of an execute, recorded without HIP."""
+    """The eager three-stream issue order of an execute, recorded without HIP."""
     n = C.c_int64()
     _check(lib().cdag_trace_execute(h, PREC[prec], int(batched), None, 0, C.byref(n), int(fail_at)))
     buf = (cdag_trace_rec * max(1, n.value))()

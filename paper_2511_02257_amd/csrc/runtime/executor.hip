@@ -27,7 +27,6 @@
 #include <cstring>
 #include <map>
 #include <mutex>
-#include <set>
 #include <string>
 #include <cstdlib>
 #include <thread>
@@ -35,6 +34,8 @@
 
 #include "../ctx.hpp"
 #include "../kernels/kernels.hpp"
+#include "graph_order.hpp"
+#include "walk.hpp"
 
 namespace cdag {
 
@@ -55,8 +56,6 @@ double now() {
   return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
 }
 
-// Stream roles; trace records and event ids use these numbers.
-enum StreamRole : int { S_COMP = 0, S_H2D = 1, S_D2H = 2, kStreams = 3 };
 // Most bytes of a step's transfers, in one direction, that are moved by a kernel
 // where copies can run beside kernels (eager issue and the three-stream graph).
 constexpr int64_t kKernelMoveBytes = 8 << 20;
@@ -368,100 +367,6 @@ int64_t launch_step(const KernelPlan& kp, int64_t g, int prec, char* arena, hipS
   return n;
 }
 
-// Where pass k of a time-chunked execution keeps its data: the tensor pool and
-// workspace of half k % 2 of the arena, half k % 2 of the host spill pool, and
-// slices [k nt / C, (k + 1) nt / C) of every tensor (bytes(u) per pass).
-struct PassMap {
-  const Ctx& c;
-  int64_t k, dev_shift, host_shift;
-  PassMap(const Ctx& ctx, int64_t pass)
-      : c(ctx), k(pass), dev_shift((pass % 2) * ctx.kplan.half_bytes),
-        host_shift((pass % 2) * ctx.plan.host_spill_bytes) {}
-  int64_t bytes(int64_t u) const { return c.plan.tsize(c.dag, u); }
-  int64_t dev(int64_t off) const { return off + dev_shift; }
-  int64_t host(int64_t off) const { return off + host_shift; }
-  int64_t stage(int64_t u) const { return k * bytes(u); }   // in the leaf's staging buffer
-  // arena offset of operand x planned at `planned`: a resident leaf's slices of
-  // this pass, else the planned offset in the pass's half
-  int64_t operand(int64_t x, int64_t planned) const {
-    if (c.plan.opts.leaves_resident && c.dag.is_leaf(x)) return c.plan.leaf_off[x] + k * bytes(x);
-    return dev(planned);
-  }
-};
-
-// Walk global execution steps [g0, g1), step s of pass k's program at a time: each
-// step's spills (after the kernels that last touched the tensor and any upload
-// still reading the host range), its uploads (after the kernels and spills
-// that last used the arena range, and the spill that wrote a re-uploaded
-// tensor), then its kernels (after the step's uploads and any spill still
-// reading an output's memory).  With one_stream (how one-stream segments are
-// captured) every dependency is the stream order and no event is used.  In a
-// captured segment, waits on steps before g0 are left out: the segments' graphs
-// run one after another on one stream, so everything before g0 has finished
-// when the segment starts.  Ops issues the work (HipOps) or records it
-// (TraceOps).
-template <class Ops>
-int64_t walk_steps(const Ctx& c, int64_t g0, int64_t g1, bool one_stream, bool in_capture, Ops& ops) {
-  const Plan& p = c.plan;
-  const int64_t C = p.chunks();
-  // waited[to][from]: newest step of stream `from` that stream `to` has waited
-  // for; events of one stream complete in step order, so older ones are implied
-  int64_t waited[kStreams][kStreams];
-  for (auto& row : waited)
-    for (auto& x : row) x = in_capture ? g0 - 1 : -1;
-  auto wait = [&](int to, int from, int64_t g) {
-    if (one_stream || g < 0 || g <= waited[to][from]) return;
-    ops.wait(to, from, g, g);
-    waited[to][from] = g;
-  };
-  int64_t n_launch = 0;
-  for (int64_t g = g0; g < g1; ++g) {
-    const int64_t k = p.pass_of(g), kS = p.xfirst(k), s = g - kS;
-    const Plan::Program& prog = p.program(k);
-    const PassMap m(c, k);
-    auto at = [&](int64_t step) { return step >= 0 ? kS + step : -1; };
-    if (s == 0 && k >= 2 && !one_stream && !(in_capture && p.xfirst(k - 1) <= g0)) {
-      // pass k - 2 used the same half of the arena and of the spill pool
-      ops.wait_pass(S_H2D, S_COMP, k - 2, g);
-      ops.wait_pass(S_H2D, S_D2H, k - 2, g);
-      ops.wait_pass(S_D2H, S_H2D, k - 2, g);
-      ops.wait_pass(S_COMP, S_D2H, k - 2, g);
-    }
-    bool any_d2h = false, any_h2d = false;
-    int64_t alloc_d2h = -1;
-    for (int64_t ri = prog.off[s]; ri < prog.off[s + 1]; ++ri) {
-      const PlanRec& r = prog.recs[ri];
-      if (r.op != OP_D2H) continue;
-      wait(S_D2H, S_COMP, at(r.wait_comp));
-      wait(S_D2H, S_H2D, at(r.wait_h2d));
-      ops.transfer(r, m, g);
-      any_d2h = true;
-    }
-    if (any_d2h && !one_stream) ops.record(S_D2H, g);
-    for (int64_t ri = prog.off[s]; ri < prog.off[s + 1]; ++ri) {
-      const PlanRec& r = prog.recs[ri];
-      if (r.op == OP_H2D) {
-        wait(S_H2D, S_COMP, at(r.wait_comp));
-        wait(S_H2D, S_D2H, at(r.wait_d2h));
-        ops.transfer(r, m, g);
-        any_h2d = true;
-      } else if (r.op == OP_ALLOC) {
-        alloc_d2h = std::max(alloc_d2h, at(r.wait_d2h));
-      }
-    }
-    if (any_h2d && !one_stream) ops.record(S_H2D, g);
-    if (any_h2d) wait(S_COMP, S_H2D, g);
-    wait(S_COMP, S_D2H, alloc_d2h);
-    n_launch += ops.launch(g, m);
-    if (!one_stream) {
-      ops.record(S_COMP, g);
-      if (s == prog.n() - 1 && k + 2 < C)
-        for (int r = 0; r < kStreams; ++r) ops.record_pass(r, k, g);
-    }
-  }
-  return n_launch;
-}
-
 // Ends of one transfer of pass m: an upload from the leaf's staging or the
 // spill pool, or a spill.
 Move move_of(const Ctx& c, const Device& D, int prec, const PlanRec& r, const PassMap& m) {
@@ -634,73 +539,27 @@ struct TraceOps {
 };
 
 // The graph form: the same walk adding the transfers and kernels to a HIP
-// graph as nodes with explicit dependencies (no stream capture).  A copy node
-// depends on the previous node of its stream and on the nodes its stream waited
-// for since; an event stands for its stream's last node (joined with that
-// stream's pending waits) at the time it is recorded.  Kernels, and a step's
-// small transfers (moved by a kernel), form one chain, the compute stream's: a
-// chain node depends on the one before it and on what it needs outside the
-// chain only, so a graph without copy nodes is a plain sequence.
+// graph as nodes with explicit dependencies (no stream capture), which
+// GraphOrder works out: kernels, and a step's small transfers (moved by a
+// kernel), are one chain; large transfers are copy nodes beside it.
 struct GraphOps {
   const Ctx& c;
   Device& D;
   int prec;
   hipGraph_t graph;
-  hipGraphNode_t last[kStreams] = {nullptr, nullptr, nullptr};
-  std::vector<hipGraphNode_t> pending[kStreams];
-  std::vector<hipGraphNode_t> ev_node[kStreams];     // per global step
-  std::vector<hipGraphNode_t> pass_node[kStreams];   // per pass
+  GraphOrder<hipGraphNode_t> order;
   std::vector<hipGraphNode_t> deps;
   std::vector<Move> moves[kStreams];                 // of the step, not yet added
-  std::set<hipGraphNode_t> chain;                    // the chain's nodes
-  bool copies = false;                               // a copy node was added
 
-  GraphOps(const Ctx& ctx, Device& dev, int p, hipGraph_t g) : c(ctx), D(dev), prec(p), graph(g) {
-    const size_t G = (size_t)ctx.plan.n_xsteps();
-    for (int r = 0; r < kStreams; ++r) {
-      ev_node[r].assign(G, nullptr);
-      pass_node[r].assign((size_t)ctx.plan.chunks(), nullptr);
-    }
-  }
-  void need(hipGraphNode_t n, bool in_chain) {
-    if (!n || (in_chain && n != last[S_COMP] && chain.count(n))) return;
-    if (std::find(deps.begin(), deps.end(), n) == deps.end()) deps.push_back(n);
-  }
-  // dependencies of stream r's next node; a chain node also follows the chain
-  void deps_of(int r, bool in_chain) {
-    deps.clear();
-    if (in_chain) need(last[S_COMP], true);
-    for (int q : {r, in_chain ? (int)S_COMP : r}) {
-      for (hipGraphNode_t n : pending[q]) need(n, in_chain);
-      need(last[q], in_chain);
-    }
-  }
-  void added(int r, hipGraphNode_t n, bool in_chain) {
-    for (int q : {r, in_chain ? (int)S_COMP : r}) {
-      last[q] = n;
-      pending[q].clear();
-    }
-    if (in_chain) chain.insert(n);
-  }
-  hipGraphNode_t head(int r) {
-    if (pending[r].empty()) return last[r];
-    deps_of(r, r == S_COMP);
-    hipGraphNode_t n = nullptr;
-    HIPC(hipGraphAddEmptyNode(&n, graph, deps.data(), deps.size()));
-    added(r, n, r == S_COMP);
-    return n;
-  }
-  void wait(int to, int from, int64_t g, int64_t) {
-    if (ev_node[from][g]) pending[to].push_back(ev_node[from][g]);
-  }
+  GraphOps(const Ctx& ctx, Device& dev, int p, hipGraph_t g)
+      : c(ctx), D(dev), prec(p), graph(g), order(ctx.plan.n_xsteps(), ctx.plan.chunks()) {}
+  void wait(int to, int from, int64_t g, int64_t) { order.wait(to, from, g); }
   void record(int r, int64_t g) {   // comes after the step's transfers on r
     flush(r);
-    ev_node[r][g] = head(r);
+    order.record(r, g);
   }
-  void wait_pass(int to, int from, int64_t k, int64_t) {
-    if (pass_node[from][k]) pending[to].push_back(pass_node[from][k]);
-  }
-  void record_pass(int r, int64_t k, int64_t) { pass_node[r][k] = head(r); }
+  void wait_pass(int to, int from, int64_t k, int64_t) { order.wait_pass(to, from, k); }
+  void record_pass(int r, int64_t k, int64_t) { order.record_pass(r, k); }
   void transfer(const PlanRec& r, const PassMap& m, int64_t) {
     moves[r.op == OP_D2H ? S_D2H : S_H2D].push_back(move_of(c, D, prec, r, m));
   }
@@ -712,12 +571,11 @@ struct GraphOps {
     for (const Move& mv : moves[r]) bytes += mv.bytes;
     if (bytes > kKernelMoveBytes) {
       for (const Move& mv : moves[r]) {
-        deps_of(r, false);
+        order.deps_of(r, false, &deps);
         hipGraphNode_t n = nullptr;
         HIPC(hipGraphAddMemcpyNode1D(&n, graph, deps.data(), deps.size(), mv.dst, mv.src, (size_t)mv.bytes,
                                      r == S_D2H ? hipMemcpyDeviceToHost : hipMemcpyHostToDevice));
-        added(r, n, false);
-        copies = true;
+        order.added(r, false, n);
       }
       moves[r].clear();
       return;
@@ -740,10 +598,10 @@ struct GraphOps {
     np.sharedMemBytes = 0;
     np.kernelParams = args;
     np.extra = nullptr;
-    deps_of(r, true);
+    order.deps_of(r, true, &deps);
     hipGraphNode_t n = nullptr;
     HIPC(hipGraphAddKernelNode(&n, graph, deps.data(), deps.size(), &np));
-    added(r, n, true);
+    order.added(r, true, n);
   }
   void kernel(KernelCall& k) {
     k.bind();
@@ -761,7 +619,7 @@ struct GraphOps {
   // The cross sums end a graph that is one chain; with copy nodes beside it
   // they are launched after the graph.
   void finish() {
-    if (copies) return;
+    if (order.copies()) return;
     KernelCall k;
     HIPC(finish_call(c.kplan, D.arena, (char*)D.results, &k));
     kernel(k);
@@ -985,7 +843,7 @@ hipGraph_t build_graph(Ctx& c, Device& D, int prec, bool* finished) {
     GraphOps ops(c, D, prec, g);
     walk_steps(c, 0, c.plan.n_xsteps(), false, false, ops);
     ops.finish();
-    *finished = !ops.copies;
+    *finished = !ops.order.copies();
   } catch (...) {
     ignore(hipGraphDestroy(g));
     throw;
@@ -1084,7 +942,7 @@ void device_execute(Ctx& c, int prec, int batched, cdag_exec_stats* st) {
   } else {
     HipOps ops{c, D, prec, {D.comp, D.copy, D.spill_s}, timed, {}};
     n_launch += walk_steps(c, 0, G, false, false, ops);
-    // the results copy and the caller's later work follow every transfer
+    // the cross sums, and the caller's later work, follow every transfer
     HIPC(hipEventRecord(D.ev_join[0], D.copy));
     HIPC(hipEventRecord(D.ev_join[1], D.spill_s));
     HIPC(hipStreamWaitEvent(D.comp, D.ev_join[0], 0));

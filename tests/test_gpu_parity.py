@@ -880,3 +880,31 @@ def test_grouped_transfers(prec, nvec, nt, chunks, n_leaves):
                 runner.run(prec, True)
                 assert np.array_equal(np.concatenate(ctx.fetch_correlators()).view(np.uint64), want), (budget, mode)
     ctx.close()
+
+
+@pytest.mark.parametrize("chunks", [5, 8])
+def test_graph_of_many_passes(chunks):
+    """Issue mode 2 over more passes than the two halves of the memory alternate
+    twice over: one graph whose nodes are a plain sequence, replayed, gives the
+    bits of resident leaves, with and without spills."""
+    import paper_2511_02257_amd as X
+    from paper_2511_02257_amd.device import DeviceRunner
+    wl = W.meson_ring(n_leaves=8, nvec=24, nt=40, n_graphs=40, lmin=4, lmax=6, sigma=24 ** -0.5, n_corr=2, seed=77)
+    ctx = X.Context()
+    ctx.build_cdag(wl.leaves, wl.graphs)
+    _, _, peak = ctx.memsim(ctx.schedule("input"), 16)
+    ctx.schedule("tree")
+    runner = DeviceRunner(ctx, 0)
+    ctx.set_options(leaves_resident=True, wave_lookahead=16)
+    runner.run("fp64", True)
+    want = np.concatenate(ctx.fetch_correlators()).view(np.uint64).copy()
+    ctx.set_time_chunks(chunks)
+    ctx.set_options(leaves_resident=False, wave_lookahead=16, use_graphs=2)
+    spills = 0
+    for budget in (None, peak // 6):
+        ctx.set_mem_budget(budget)
+        for _ in range(3):
+            spills += runner.run("fp64", True)["plan"]["n_d2h"]
+            assert np.array_equal(np.concatenate(ctx.fetch_correlators()).view(np.uint64), want), budget
+    assert spills > 0
+    ctx.close()

@@ -538,3 +538,73 @@ def test_long_items_keep_short_steps_as_planned(policy):
     c.close()
     assert n[16][1] == n[16][0]
     assert n[B.LOOKAHEAD_ALL][1] > n[B.LOOKAHEAD_ALL][0]
+
+
+def overlaps_within_steps(trace):
+    """Accesses of one step's kernels, which run side by side, to the same bytes,
+    at least one of them a write (an output over memory that another contraction
+    of the step, or its own, still uses): the number of accesses that meet an
+    earlier one, in order of their first byte."""
+    steps = {}
+    for r in trace:
+        if r["stream"] == 0 and r["op"] in ("read", "write"):
+            steps.setdefault(r["seq"], []).append((r["off"], r["off"] + r["bytes"], r["op"] == "write"))
+    n_bad = 0
+    for acc in steps.values():
+        end = end_w = -1
+        for lo, hi, w in sorted(acc):
+            n_bad += lo < (end if w else end_w)
+            end = max(end, hi)
+            if w:
+                end_w = max(end_w, hi)
+    return n_bad
+
+
+@pytest.mark.parametrize("chunks,resident,mode,wave_max", [(1, False, 0, 4096), (1, True, 1, 4096), (2, False, 0, 4096),
+                                                           (2, False, 2, 4096), (1, False, 1, 3)])
+def test_outputs_of_a_step_overlap_nothing_it_uses(chunks, resident, mode, wave_max):
+    """In every issue order, and at every lookahead, no contraction's output lies
+    over memory that its own execution step reads or writes; an output moved
+    over an operand of the same step is found."""
+    cases = _chunk_cases_small() + [("staged", _staged_case())]
+    cases += [(f"ring{s}", W.meson_ring(n_leaves=6, nvec=6, nt=2, n_graphs=30, lmin=3, lmax=6, seed=s, with_data=False))
+              for s in range(80, 86)]
+    merged = 0
+    for name, wl in cases:
+        c = _ctx(wl)
+        c.set_time_chunks(chunks)
+        for policy in ("input", "tree"):
+            c.schedule(policy)
+            for look in (0, 2, 16, B.LOOKAHEAD_ALL):
+                for budget in (None, 1 << 40):   # with room beyond the tightest placement, and without
+                    c.set_mem_budget(budget)
+                    c.set_options(leaves_resident=resident, wave_lookahead=look, wave_max=wave_max, use_graphs=mode)
+                    p = c.plan("fp64", True)
+                    t = c.trace_execute("fp64", True)
+                    assert overlaps_within_steps(t) == 0
+                    merged += len({r["step"] for r in t if r["op"] == "read" and r["stream"] == 0}) < p["n_steps"]
+        c.close()
+    assert merged > 20
+    k = next(i for i, r in enumerate(t) if r["op"] == "write" and r["stream"] == 0)
+    assert t[k - 1]["op"] == "read" and t[k - 1]["seq"] == t[k]["seq"]
+    planted = list(t)
+    planted[k] = dict(t[k], off=t[k - 1]["off"] + t[k - 1]["bytes"] - 16)
+    assert overlaps_within_steps(planted) > 0
+
+
+@pytest.mark.parametrize("name,policy,chunks,look", [("baryon_mix", "sibling", 8, 16), ("baryon_mix", "tree", 8, B.LOOKAHEAD_ALL),
+                                                     ("baryon_mix", "tree", 1, 64), ("meson_ring", "tree", 16, 384),
+                                                     ("meson_ring", "tree", 1, 16), ("batched", "tree", 8, B.LOOKAHEAD_ALL)])
+def test_outputs_of_a_step_overlap_nothing_it_uses_at_full_size(name, policy, chunks, look):
+    wl = W.config(name, with_data=False)
+    prec = "fp32" if name == "batched" else "fp64"
+    c = _ctx(wl)
+    c.schedule("input")
+    budget = c.plan("fp64", False)["peak_live"] // 4 if name == "meson_ring" else wl.budget_bytes
+    c.schedule(policy)
+    c.set_mem_budget(budget)
+    c.set_time_chunks(chunks)
+    c.set_options(wave_lookahead=look, use_graphs=0)
+    t = c.trace_execute(prec, True)
+    c.close()
+    assert overlaps_within_steps(t) == 0

@@ -498,23 +498,24 @@ int cdag_execute_static(cdag_ctx* c, int prec, int batched, cdag_exec_stats* out
 
 /* Autotuner over the kernel variants of cdag_set_tile, for every distinct
  * (kind, N) among the exterior contractions of the DAG.  mode 0 (synthetic):
- * time each variant and split_k setting `reps` times on a batch of time
- * slices of that shape (at least 4096 work items, as in a wave of such
- * contractions, at most 64 contractions' worth; split counts as for one
- * contraction) placed in the bound arena's tensor pool (as planned for
- * (prec, batched); its contents are scratch between executes) and keep the
- * fastest per time slice.  mode 1 (in situ): execute the planned DAG `reps` times per
- * variant and split_k setting, shape by shape, with launch timing on, and keep
- * the least time of exterior contractions and split-K reductions in the
- * fastest of the reps
- * (needs leaf data; costs up to 40 * reps executes per shape).  mode 2
- * (synthetic, uniform): the timings of mode 0, then one choice for every
- * shape, the one whose summed time over the DAG (time per slice times the
- * slices of each shape) is least, so that each wave's exterior contractions
- * run in one grouped launch.  *n_tuned
- * (nullable) receives the number of shapes tuned.  Needs cdag_bind_device and
- * an arena of at least the plan's arena_bytes; invalidates the current plan
- * and results. */
+ * time each variant and split_k setting, and what runs without a choice,
+ * `reps` times on a batch of time slices of that shape (at least 4096 work
+ * items, as in a wave of such contractions, at most 64 contractions' worth;
+ * split counts as for one contraction) placed in the bound arena's tensor pool
+ * (as planned for (prec, batched); its contents are scratch between executes)
+ * and keep the fastest per time slice.  mode 1 (in situ): execute the planned
+ * DAG `reps` times per variant and split_k setting, and without a choice, shape
+ * by shape, with launch timing on, and keep the least time of exterior
+ * contractions and split-K reductions in the fastest of the reps (needs leaf
+ * data; costs up to 49 * reps executes per shape).  mode 2 (synthetic,
+ * uniform): the timings of mode 0, then one choice for every shape, the one
+ * whose summed time over the DAG (time per slice times the slices of each
+ * shape) is least, so that each wave's exterior contractions run in one
+ * grouped launch.  A shape whose best choice is not faster than none is left
+ * without one (mode 2: all shapes, where one variant runs them all without a
+ * choice).  *n_tuned (nullable) receives the number of shapes
+ * decided.  Needs cdag_bind_device and an arena of at least the plan's
+ * arena_bytes; invalidates the current plan and results. */
 int cdag_autotune(cdag_ctx* c, int prec, int batched, int reps, int mode, int64_t* n_tuned);
 
 /* fetch_correlators -- Sec. I and Sec. II-B: the value of each graph, the

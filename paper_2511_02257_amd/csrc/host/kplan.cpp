@@ -171,6 +171,64 @@ int default_tile(int prec, int kind, int n) {
   return choice_of(variant_of(tile, 1), true);
 }
 
+// decompose() for a contraction of (kind, N) without a choice: the K splits of
+// default_tile(), in the tiles of default_variant().
+static int decompose_default(const Gemm& g, int nt, int prec, int kind, int n, HecDesc* h, int nt_run = 0) {
+  const int choice = default_tile(prec, kind, n);
+  decompose(g, nt, choice, prec, h, nt_run);
+  const int v = default_variant(prec, choice_variant(choice), g);
+  retile(v, h);
+  return v;
+}
+
+int decompose_candidate(const Gemm& g, int nt, int choice, int prec, int kind, int n, HecDesc* h) {
+  if (choice == kNoChoice) return decompose_default(g, nt, prec, kind, n, h);
+  decompose(g, nt, choice, prec, h);
+  return choice_variant(choice);
+}
+
+int64_t store_choices(const std::map<std::pair<int, int>, TuneRow>& rows, int prec, bool uniform, TileTable* tiles) {
+  // fastest choice by t(choice), or kNoChoice; -1 where nothing was timed
+  auto pick = [](auto&& t, bool may_have_none) {
+    int best = -1;
+    for (int ch = 0; ch < kNumChoices; ++ch)
+      if (t(ch) < kNotTimed && (best < 0 || t(ch) < t(best))) best = ch;
+    const bool none = may_have_none && t(kNoChoice) < kNotTimed;
+    return none && (best < 0 || t(kNoChoice) <= t(best)) ? (int)kNoChoice : best;
+  };
+  auto store = [&](const std::pair<int, int>& shape, int ch) {
+    const auto key = std::make_tuple(prec, shape.first, shape.second);
+    if (ch == kNoChoice) tiles->erase(key);
+    else (*tiles)[key] = ch;
+  };
+  int64_t n = 0;
+  if (!uniform) {
+    for (const auto& kv : rows) {
+      const int ch = pick([&](int c) { return kv.second.t[c]; }, true);
+      if (ch < 0) continue;
+      store(kv.first, ch);
+      ++n;
+    }
+    return n;
+  }
+  if (rows.empty()) return 0;
+  bool one_variant = true;
+  for (const auto& kv : rows) one_variant &= kv.second.default_variant == rows.begin()->second.default_variant;
+  const int ch = pick(
+      [&](int c) {
+        double t = 0;
+        for (const auto& kv : rows) {
+          if (kv.second.t[c] >= kNotTimed) return kNotTimed;
+          t += kv.second.weight * kv.second.t[c];
+        }
+        return t;
+      },
+      one_variant);
+  if (ch < 0) return 0;
+  for (const auto& kv : rows) store(kv.first, ch);
+  return (int64_t)rows.size();
+}
+
 // Descriptor (without offsets) of exterior contraction u over nt_run of its time
 // slices; returns the kernel variant that runs it.  The split-K decision is the
 // contraction's own (independent of batching), so results do not depend on how
@@ -184,12 +242,9 @@ static int contraction_of(const Dag& d, int64_t u, int prec, const TileTable& ti
     return kGenVariant;
   }
   const auto it = tiles.find(std::make_tuple(prec, (int)d.kind[u], (int)d.nvec[u]));
-  const int choice = it != tiles.end() ? it->second : default_tile(prec, d.kind[u], d.nvec[u]);
-  decompose(g, d.nt[u], choice, prec, h, nt_run);
-  if (it != tiles.end()) return choice_variant(choice);
-  const int v = default_variant(prec, choice_variant(choice), g);
-  retile(v, h);
-  return v;
+  if (it == tiles.end()) return decompose_default(g, d.nt[u], prec, d.kind[u], d.nvec[u], h, nt_run);
+  decompose(g, d.nt[u], it->second, prec, h, nt_run);
+  return choice_variant(it->second);
 }
 
 std::vector<double> item_flops(const Dag& d, int prec, const TileTable& tiles) {

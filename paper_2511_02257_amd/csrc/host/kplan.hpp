@@ -77,6 +77,27 @@ int default_variant(int prec, int variant, const Gemm& g);
 // general kind can occur with several operand ranks).
 struct TuneShape { int nt; Gemm gemm; };
 std::map<std::pair<int, int>, TuneShape> tune_shapes(const Dag& d);
+// No choice, as one more candidate of the autotuners.
+constexpr int kNoChoice = kNumChoices;
+// decompose() for a tuner's candidate: `choice`, or kNoChoice for what runs a
+// contraction of (kind, N) without an entry.  Returns the kernel variant.
+int decompose_candidate(const Gemm& g, int nt, int choice, int prec, int kind, int n, HecDesc* h);
+// Times of one shape's candidates (kNumChoices choices, then kNoChoice; kNotTimed
+// where a candidate did not run), the shape's share of the DAG and the variant
+// that runs it without a choice.
+constexpr double kNotTimed = 1e300;
+struct TuneRow {
+  std::vector<double> t = std::vector<double>(kNumChoices + 1, kNotTimed);
+  double weight = 1.0;
+  int default_variant = -1;
+};
+// Enter the fastest choice of each shape, or (uniform) the one choice whose
+// weighted time over all shapes is least, into the table; where it is not
+// faster than no choice, the entry is removed instead (uniform: where one
+// variant runs every shape without a choice, so that launches stay grouped).
+// A shape of which nothing was timed keeps what it has.  Returns the number of
+// shapes decided.
+int64_t store_choices(const std::map<std::pair<int, int>, TuneRow>& rows, int prec, bool uniform, TileTable* tiles);
 // k-step of the matrix-core kernels: FP64 uses 16, FP32 and split-BF16 32.
 inline int k_step(int prec) { return prec == 0 ? 16 : 32; }
 // Split-K: aim for at least this many work items per contraction, keeping at

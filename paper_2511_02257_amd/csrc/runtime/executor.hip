@@ -630,13 +630,14 @@ constexpr int64_t kSegmentSteps = 64;   // steps per one-stream graph when trans
 }  // namespace
 
 // Autotuner: for every distinct (kind, N) among the exterior contractions,
-// time each kernel choice on a synthetic contraction of that shape (operands
-// in the arena's tensor pool, which holds nothing between executes).  uniform
-// = false keeps the fastest choice per time slice of each shape; uniform =
-// true keeps the one choice whose time over the whole DAG (per-slice time x
-// the slices of that shape in the DAG, summed over shapes) is least, so that
-// every wave runs its exterior contractions in one grouped launch.  The
-// choices enter the tile table of the context.
+// time each kernel choice, and what runs without one, on a synthetic
+// contraction of that shape (operands in the arena's tensor pool, which holds
+// nothing between executes).  uniform = false keeps the fastest per time slice
+// of each shape; uniform = true keeps the one choice whose time over the whole
+// DAG (per-slice time x the slices of that shape in the DAG, summed over
+// shapes) is least, so that every wave runs its exterior contractions in one
+// grouped launch.  The choices enter the tile table of the context
+// (store_choices()).
 int64_t device_autotune(Ctx& c, int prec, int batched, int reps, bool uniform) {
   Device& D = *c.dev;
   HIPC(hipSetDevice(D.device));
@@ -650,31 +651,31 @@ int64_t device_autotune(Ctx& c, int prec, int batched, int reps, bool uniform) {
   auto al = [](int64_t x) { return (x + 255) / 256 * 256; };
   const int64_t lo = al(p.leaf_region_bytes), hi = kp.ws_off + kp.ws_bytes;
   const auto shapes = tune_shapes(c.dag);
+  std::map<std::pair<int, int>, TuneRow> rows;   // time per slice, per candidate
+  for (const auto& sh : shapes) rows[sh.first].weight = 0.0;
   // slices of each shape in the DAG (the uniform choice's weights)
-  std::map<std::pair<int, int>, double> weight;
-  for (int64_t u = c.dag.n_leaves; u < c.dag.n_nodes(); ++u)
-    if (c.dag.kind[u] != HCA) weight[{c.dag.kind[u], c.dag.nvec[u]}] += c.dag.nt[u];
-  std::map<std::pair<int, int>, std::vector<double>> per_slice;   // shape -> time per slice, per choice
+  for (int64_t u = c.dag.n_leaves; u < c.dag.n_nodes(); ++u) {
+    const auto row = rows.find({c.dag.kind[u], c.dag.nvec[u]});
+    if (row != rows.end()) row->second.weight += c.dag.nt[u];
+  }
   hipEvent_t e0, e1;
   HIPC(hipEventCreate(&e0));
   HIPC(hipEventCreate(&e1));
-  int64_t tuned = 0;
   try {
     for (const auto& sh : shapes) {
-      const int kind = sh.first.first, n = sh.first.second;
-      double best = 1e300;
-      int best_tile = -1;
-      const int snt = sh.second.nt;
-      std::vector<double>& row = per_slice[sh.first];
-      row.assign(kNumChoices, 1e300);
-      for (int ch = 0; ch < kNumChoices; ++ch) {
+      const int kind = sh.first.first, n = sh.first.second, snt = sh.second.nt;
+      TuneRow& row = rows[sh.first];
+      for (int ch = 0; ch <= kNoChoice; ++ch) {
         HecDesc h{};
-        decompose(sh.second.gemm, snt, ch, prec, &h);   // split count of a real contraction
-        if (!choice_split_k(ch)) {
+        // split count of a real contraction
+        const int v = decompose_candidate(sh.second.gemm, snt, ch, prec, kind, n, &h);
+        if (ch == kNoChoice) {
+          row.default_variant = v;
+        } else if (!choice_split_k(ch)) {
           HecDesc a{};
-          decompose(sh.second.gemm, snt, choice_variant(ch), prec, &a);
+          decompose(sh.second.gemm, snt, v, prec, &a);
           if (a.splits == 1) {                          // same work items as the split choice
-            row[ch] = row[choice_of(choice_variant(ch), true)];
+            row.t[ch] = row.t[choice_of(v, true)];
             continue;
           }
         }
@@ -704,7 +705,6 @@ int64_t device_autotune(Ctx& c, int prec, int batched, int reps, bool uniform) {
         HIPC(hipMemsetAsync(D.arena + a, 0, (size_t)(ws - a), D.comp));
         HIPC(hipMemcpyAsync(D.arena + desc, &h, sizeof(h), hipMemcpyHostToDevice, D.comp));
         HIPC(hipMemcpyAsync(D.arena + desc + 128, &r, sizeof(r), hipMemcpyHostToDevice, D.comp));
-        const int v = choice_variant(ch);
         const bool interior =
             hec_interior(h, kTileShapes[variant_tile(v)].bm, kTileShapes[variant_tile(v)].bn, k_step(prec));
         auto once = [&] {
@@ -718,28 +718,8 @@ int64_t device_autotune(Ctx& c, int prec, int batched, int reps, bool uniform) {
         HIPC(hipEventSynchronize(e1));
         float ms = 0;
         HIPC(hipEventElapsedTime(&ms, e0, e1));
-        const double t_slice = ms / reps / (double)nt;
-        row[ch] = t_slice;
-        if (t_slice < best) { best = t_slice; best_tile = ch; }
+        row.t[ch] = ms / reps / (double)nt;
       }
-      if (best_tile >= 0 && !uniform) {
-        c.tiles[std::make_tuple(prec, kind, n)] = best_tile;
-        ++tuned;
-      }
-    }
-    if (uniform && !per_slice.empty()) {
-      double best = 1e300;
-      int best_ch = -1;
-      for (int ch = 0; ch < kNumChoices; ++ch) {
-        double t = 0;
-        for (const auto& kv : per_slice) t += weight[kv.first] * kv.second[ch];
-        if (t < best) { best = t; best_ch = ch; }
-      }
-      if (best_ch >= 0 && best < 1e299)
-        for (const auto& kv : per_slice) {
-          c.tiles[std::make_tuple(prec, kv.first.first, kv.first.second)] = best_ch;
-          ++tuned;
-        }
     }
   } catch (...) {
     ignore(hipEventDestroy(e0));
@@ -749,14 +729,14 @@ int64_t device_autotune(Ctx& c, int prec, int batched, int reps, bool uniform) {
   ignore(hipEventDestroy(e0));
   ignore(hipEventDestroy(e1));
   HIPC(hipStreamSynchronize(D.comp));
-  return tuned;
+  return store_choices(rows, prec, uniform, &c.tiles);
 }
 
 // In-situ autotuner: for every distinct (kind, N) in turn, run the planned DAG
-// `reps` times with each kernel variant for that shape (the other shapes keep
-// their current choice), with HIP events around every launch, and keep the
-// variant whose fastest execute spends the least time in exterior
-// contractions plus split-K reductions.
+// `reps` times with each kernel choice, and without one, for that shape (the
+// other shapes keep their current choice), with HIP events around every
+// launch, and keep the one whose fastest execute spends the least time in
+// exterior contractions plus split-K reductions.
 int64_t device_autotune_insitu(Ctx& c, int prec, int batched, int reps) {
   const auto shapes = tune_shapes(c.dag);
   const bool timing = c.timing;
@@ -766,16 +746,16 @@ int64_t device_autotune_insitu(Ctx& c, int prec, int batched, int reps) {
   try {
     for (const auto& sh : shapes) {
       const auto key = std::make_tuple(prec, sh.first.first, sh.first.second);
-      double best = 1e300;
-      int best_v = -1;
-      for (int v = 0; v < kNumChoices; ++v) {
-        if (!choice_split_k(v)) {
+      TuneRow row;
+      for (int v = 0; v <= kNoChoice; ++v) {
+        if (v < kNumChoices && !choice_split_k(v)) {
           // the no-split setting only differs where the rule would split
           HecDesc h{};
           decompose(sh.second.gemm, sh.second.nt, choice_variant(v), prec, &h);
           if (h.splits == 1) continue;
         }
-        c.tiles[key] = v;
+        if (v == kNoChoice) c.tiles.erase(key);
+        else c.tiles[key] = v;
         c.version++;
         plan_for_arena(c, prec, batched);
         if ((uint64_t)c.kplan.total_bytes > c.dev->arena_bytes) continue;
@@ -788,14 +768,10 @@ int64_t device_autotune_insitu(Ctx& c, int prec, int batched, int reps) {
             if (rec.type == CDAG_LAUNCH_HEC || rec.type == CDAG_LAUNCH_REDUCE) tr += rec.ms;
           t = std::min(t, tr);
         }
-        if (t < best) { best = t; best_v = v; }
+        row.t[v] = t;
       }
-      if (best_v >= 0) {
-        c.tiles[key] = best_v;
-        ++tuned;
-      } else {
-        c.tiles.erase(key);
-      }
+      c.tiles.erase(key);                        // where not one of them fits the arena
+      tuned += store_choices({{sh.first, row}}, prec, false, &c.tiles);
       c.version++;
     }
   } catch (...) {

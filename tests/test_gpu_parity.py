@@ -908,3 +908,27 @@ def test_graph_of_many_passes(chunks):
             assert np.array_equal(np.concatenate(ctx.fetch_correlators()).view(np.uint64), want), budget
     assert spills > 0
     ctx.close()
+
+
+@pytest.mark.parametrize("mode", ["synthetic", "uniform", "in_situ"])
+@pytest.mark.parametrize("prec,nvec", [("fp64", 72), ("fp32", 66), ("bf16x6", 72)])
+def test_autotune_where_no_choice_is_a_candidate(prec, nvec, mode):
+    """Sizes whose default runs a tile that cannot be chosen: every mode of the
+    autotuner times it too, decides both shapes (K32, K33), and what it keeps is
+    within the precision's bound."""
+    import paper_2511_02257_amd as X
+    from paper_2511_02257_amd.device import DeviceRunner
+    wl = W.baryon_mix(n_bar=2, n_mes=3, nvec=nvec, nt=2, n_graphs=3, n_corr=2, seed=78, sigma=1 / nvec)
+    ref = OV.correlators(wl)
+    ctx = X.Context()
+    ctx.build_cdag(wl.leaves, wl.graphs)
+    ctx.schedule("tree")
+    runner = DeviceRunner(ctx, 0)
+    assert runner.autotune(prec, True, reps=1, in_situ=mode == "in_situ", uniform=mode == "uniform") == 2
+    runner.run(prec, True)
+    corr = ctx.fetch_correlators()
+    ctx.close()
+    want, got = np.concatenate([ref[g] for g in ref]), np.concatenate([corr[g] for g in ref])
+    err = np.linalg.norm(got - want) / np.linalg.norm(want)
+    print(f"N={nvec} {prec} {mode}: rel {err:.3e}")
+    assert err <= TOL[prec]

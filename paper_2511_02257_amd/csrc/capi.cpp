@@ -51,13 +51,18 @@ int elem_bytes_prec(int prec) {
 }  // namespace
 
 namespace cdag {
-void ensure_plan(Ctx& c, int prec, int batched) {
+void ensure_plan(Ctx& c, int prec, int batched, uint64_t arena) {
   need(c.built, CDAG_E_STATE, "build_cdag first");
   need(!c.dag.general, CDAG_E_STATE, "a general DAG has no tensor shapes: it can be scheduled and simulated only");
   need(c.scheduled, CDAG_E_STATE, "schedule first");
   const int eb = elem_bytes_prec(prec);
   batched = batched ? 1 : 0;
-  if (c.planned && c.plan_version == c.version && c.plan_prec == prec && c.plan_batched == batched) return;
+  auto wider = [&] { return c.plan.halves() * (c.plan.pool_bytes - c.plan.tight_pool_bytes); };
+  if (c.planned && c.plan_version == c.version && c.plan_prec == prec && c.plan_batched == batched) {
+    const bool as_it_is = c.plan_wide_bytes > 0 ? (uint64_t)c.plan_wide_bytes > arena
+                                                : wider() == 0 || (uint64_t)c.kplan.total_bytes <= arena;
+    if (arena == NO_ARENA || as_it_is) return;
+  }
   c.planned = false;
   double t0 = now();
   PlanOpts o;
@@ -69,7 +74,6 @@ void ensure_plan(Ctx& c, int prec, int batched) {
   o.leaves_resident = c.leaves_resident;
   o.t_chunks = c.t_chunks;
   o.overlap = c.use_graphs == 0;
-  o.spread = c.spread;
   // measured on the K = 64 contractions: FP64, FP32, split BF16 in two and three pieces
   constexpr double kFlopRate[4] = {65e12, 110e12, 200e12, 140e12};
   o.flop_rate = kFlopRate[prec];
@@ -77,15 +81,17 @@ void ensure_plan(Ctx& c, int prec, int batched) {
   c.plan.opts.item_flops = item_flops(c.dag, prec, c.tiles);
   place(c.dag, c.plan);
   c.kplan = make_kernel_plan(c.dag, c.plan, prec, c.tiles, c.fuse_traces);
-  // a plan that fits the static scratch (with its staging of the largest leaf)
-  // in the tightest placement keeps to it where the wider one would not fit
-  const int64_t wider = c.plan.halves() * (c.plan.pool_bytes - c.plan.tight_pool_bytes);
-  if (wider > 0) {
+  // the tightest placement where only that fits the arena, or the static scratch
+  // (with its staging of the largest leaf)
+  c.plan_wide_bytes = 0;
+  if (wider() > 0) {
     int64_t leaf = 0;
     for (int64_t u = 0; u < c.dag.n_leaves; ++u)
       leaf = std::max<int64_t>(leaf, c.dag.elems(u) * (c.leaf_dtype[u] == CDAG_C64 ? 8 : 16));
     const int64_t need_bytes = c.kplan.total_bytes + leaf + 1024;   // 1024: the alignments of either layout
-    if (need_bytes > CDAG_STATIC_SCRATCH_BYTES && need_bytes - wider <= CDAG_STATIC_SCRATCH_BYTES + 2048) {
+    const bool scratch = need_bytes > CDAG_STATIC_SCRATCH_BYTES && need_bytes - wider() <= CDAG_STATIC_SCRATCH_BYTES + 2048;
+    if (scratch || (uint64_t)c.kplan.total_bytes > arena) {
+      if (!scratch) c.plan_wide_bytes = c.kplan.total_bytes;
       c.plan.opts.spread = false;
       place(c.dag, c.plan);
       c.kplan = make_kernel_plan(c.dag, c.plan, prec, c.tiles, c.fuse_traces);

@@ -37,8 +37,6 @@ struct Ctx {
   int64_t t_chunks = 1;
   bool fuse_traces = true;       // a step's traces ride in one of its contraction launches
   bool timing = false;
-  bool spread = true;            // plans may take more than the tightest pool (off while the bound
-                                 // arena only holds that)
   TileTable tiles;               // (prec, kind, N) -> kernel variant overrides
   uint64_t version = 1;          // bumped by every change that invalidates a plan
   // last plan
@@ -48,6 +46,8 @@ struct Ctx {
   int plan_prec = -1, plan_batched = -1;
   Plan plan;
   KernelPlan kplan;
+  int64_t plan_wide_bytes = 0;   // arena of the wider placement that the plan gave up for a smaller
+                                 // arena (0: it did not)
   int64_t peak_post = 0, peak_live = 0;
   double t_plan = 0;
   // device
@@ -58,8 +58,12 @@ struct Ctx {
   std::vector<cdag_launch_record> records;    // per launch of the last timed execute
 };
 
-// Plans for (prec, batched) unless the cached plan already matches.
-void ensure_plan(Ctx& c, int prec, int batched);
+// Plans for (prec, batched) unless the cached plan already matches.  arena:
+// bytes that the plan is to run in, in the tightest placement if only that
+// fits them (a plan made for a smaller arena is made again where the wider
+// placement fits); NO_ARENA takes the plan as it is.
+constexpr uint64_t NO_ARENA = UINT64_MAX;
+void ensure_plan(Ctx& c, int prec, int batched, uint64_t arena = NO_ARENA);
 
 void device_destroy(Device* d);
 void device_bind(Ctx& c, int device, void* compute_stream, void* copy_stream);

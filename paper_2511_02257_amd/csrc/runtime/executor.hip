@@ -215,22 +215,10 @@ void device_bind_arena(Ctx& c, void* arena, uint64_t bytes) {
   c.dev->arena = (char*)arena;
   c.dev->arena_bytes = bytes;
   c.dev->arena_epoch++;
-  if (!c.spread) {
-    c.spread = true;
-    c.version++;
-  }
 }
 
-// Plan for (prec, batched), in the tightest placement where the bound arena
-// does not hold the wider one.
-static void plan_for_arena(Ctx& c, int prec, int batched) {
-  ensure_plan(c, prec, batched);
-  if ((uint64_t)c.kplan.total_bytes > c.dev->arena_bytes && c.plan.pool_bytes > c.plan.tight_pool_bytes) {
-    c.spread = false;
-    c.version++;
-    ensure_plan(c, prec, batched);
-  }
-}
+// Plan for (prec, batched) in the bound arena.
+static void plan_for_arena(Ctx& c, int prec, int batched) { ensure_plan(c, prec, batched, c.dev->arena_bytes); }
 
 namespace {
 // Interleaved complex [nt][e] (S = double or float) -> planar [nt][2][e] in T.
@@ -641,10 +629,10 @@ constexpr int64_t kSegmentSteps = 64;   // steps per one-stream graph when trans
 int64_t device_autotune(Ctx& c, int prec, int batched, int reps, bool uniform) {
   Device& D = *c.dev;
   HIPC(hipSetDevice(D.device));
+  if (!D.arena) throw Error(CDAG_E_STATE, "cdag_bind_arena first");
   plan_for_arena(c, prec, batched);
   const Plan& p = c.plan;
   const KernelPlan& kp = c.kplan;
-  if (!D.arena) throw Error(CDAG_E_STATE, "cdag_bind_arena first");
   if ((uint64_t)kp.total_bytes > D.arena_bytes) throw Error(CDAG_E_NOMEM, "arena smaller than the plan");
   (void)batched;
   const int64_t eb = prec == CDAG_FP64 ? 16 : 8, acc = prec == CDAG_FP64 ? 8 : 4;

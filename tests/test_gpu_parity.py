@@ -932,3 +932,44 @@ def test_autotune_where_no_choice_is_a_candidate(prec, nvec, mode):
     err = np.linalg.norm(got - want) / np.linalg.norm(want)
     print(f"N={nvec} {prec} {mode}: rel {err:.3e}")
     assert err <= TOL[prec]
+
+
+def test_arena_that_holds_only_the_tightest_placement():
+    """An arena too small for a plan's wider placement runs the tightest one, for
+    that plan alone: the same bits; another precision whose wider placement
+    fits keeps it; the plan stays good for the static execute when an arena is
+    bound again, and a large one brings the wider placement back."""
+    import torch
+    import paper_2511_02257_amd as X
+    wl = W.meson_ring(n_leaves=8, nvec=32, nt=4, n_graphs=60, lmin=4, lmax=6, seed=79, sigma=32 ** -0.5, n_corr=2)
+    ctx = X.Context()
+    ctx.build_cdag(wl.leaves, wl.graphs)
+    ctx.schedule("tree")
+    size = {p: ctx.plan(p, True)["arena_bytes"] for p in ("fp64", "fp32")}
+    assert size["fp32"] < size["fp64"]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    ctx.bind_device(0, *[s.cuda_stream for s in streams])
+    large = torch.empty(size["fp64"], dtype=torch.uint8, device="cuda")
+    small = torch.empty(size["fp32"], dtype=torch.uint8, device="cuda")
+
+    def bits(run):
+        st = run("fp64", True)
+        return st["plan"]["arena_bytes"], np.concatenate(ctx.fetch_correlators()).view(np.uint64)
+    ctx.bind_arena(large.data_ptr(), large.numel())
+    n, want = bits(ctx.execute)
+    assert n == size["fp64"]
+    ctx.bind_arena(small.data_ptr(), small.numel())
+    for _ in range(2):
+        n, got = bits(ctx.execute)
+        assert n < small.numel() and np.array_equal(got, want)
+    assert ctx.plan("fp64", True)["arena_bytes"] == n      # the plan in force, not made again
+    ctx.execute("fp32", True)
+    assert ctx.plan("fp32", True)["arena_bytes"] == size["fp32"]
+    ctx.execute("fp64", True)
+    ctx.plan("fp64", True)
+    ctx.bind_arena(large.data_ptr(), large.numel())
+    n_static, got = bits(ctx.execute_static)               # binding an arena leaves the plan as it is
+    assert n_static == n and np.array_equal(got, want)
+    n, got = bits(ctx.execute)
+    assert n == size["fp64"] and np.array_equal(got, want)
+    ctx.close()

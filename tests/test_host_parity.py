@@ -648,3 +648,21 @@ def test_index_pair_specs_build_and_validation():
     with pytest.raises(X.CdagError) as e:                  # a kind with no spec
         X.Context().build_cdag(L, [W.GraphSpec([(W.SPEC_BASE + 1, 0, 1), (W.HCA, -1, 2)])], [])
     assert e.value.code == B.E_INVALID
+
+
+def test_plan_keeps_to_the_static_scratch_where_only_its_tightest_placement_fits():
+    """Without a budget a plan may be placed wider than it has to; where the wider
+    placement would not fit the static scratch (with the largest leaf staged)
+    and the tightest does, the tightest is taken."""
+    need = {}
+    for nvec in (48, 64):
+        wl = W.meson_ring(n_leaves=8, nvec=nvec, nt=8, n_graphs=60, lmin=4, lmax=6, seed=79, with_data=False)
+        c = X.Context()
+        c.build_cdag(wl.leaves, wl.graphs)
+        c.schedule("tree")
+        wide = c.plan("fp64", True)["arena_bytes"]
+        c.set_mem_budget(1 << 50)            # a budget: the tightest placement
+        need[nvec] = wide, c.plan("fp64", True)["arena_bytes"], 8 * 16 * nvec ** 2
+        c.close()
+    assert need[48][0] > need[48][1] and need[48][0] + need[48][2] <= B.STATIC_SCRATCH_BYTES
+    assert need[64][0] == need[64][1] <= B.STATIC_SCRATCH_BYTES // 4

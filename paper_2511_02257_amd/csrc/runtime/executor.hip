@@ -638,6 +638,9 @@ int64_t device_autotune(Ctx& c, int prec, int batched, int reps, bool uniform) {
   const int64_t eb = prec == CDAG_FP64 ? 16 : 8, acc = prec == CDAG_FP64 ? 8 : 4;
   auto al = [](int64_t x) { return (x + 255) / 256 * 256; };
   const int64_t lo = al(p.leaf_region_bytes), hi = kp.ws_off + kp.ws_bytes;
+  // without resident leaves the synthetic operands lie where a resident plan
+  // keeps its leaves, so its next execute uploads them again
+  if (!c.leaves_resident) D.resident_prec = -1;
   const auto shapes = tune_shapes(c.dag);
   std::map<std::pair<int, int>, TuneRow> rows;   // time per slice, per candidate
   for (const auto& sh : shapes) rows[sh.first].weight = 0.0;
@@ -845,6 +848,7 @@ void device_execute(Ctx& c, int prec, int batched, cdag_exec_stats* st) {
   // leaves kept resident in their own region: one upload per (precision, arena, build)
   if (c.leaves_resident &&
       (D.resident_prec != prec || D.resident_epoch != D.arena_epoch || D.resident_key != D.stage_version[prec])) {
+    D.resident_prec = -1;                        // until every leaf is there
     for (int64_t u = 0; u < c.dag.n_leaves; ++u)
       HIPC(hipMemcpyAsync(D.arena + p.leaf_off[u], D.stage[prec][u], (size_t)c.dag.size(u, eb),
                           hipMemcpyHostToDevice, D.copy));

@@ -973,3 +973,27 @@ def test_arena_that_holds_only_the_tightest_placement():
     n, got = bits(ctx.execute)
     assert n == size["fp64"] and np.array_equal(got, want)
     ctx.close()
+
+
+def test_synthetic_autotune_between_resident_executes():
+    """The synthetic autotuner, run with the leaves on the host, writes the memory
+    where resident leaves lie; the next resident execute gives the same
+    correlators as the one before (kernel choices set back, so the same bits)."""
+    import paper_2511_02257_amd as X
+    from paper_2511_02257_amd.device import DeviceRunner
+    wl = W.meson_ring(n_leaves=6, nvec=32, nt=4, n_graphs=12, lmin=3, lmax=5, seed=81, sigma=32 ** -0.5)
+    ctx = X.Context()
+    ctx.build_cdag(wl.leaves, wl.graphs)
+    ctx.schedule("tree")
+    runner = DeviceRunner(ctx, 0)
+    runner.ensure_arena(64 << 20)
+    got = []
+    for _ in range(2):
+        ctx.set_options(leaves_resident=True)
+        runner.run("fp64", True)
+        got.append(np.concatenate(ctx.fetch_correlators()).view(np.uint64))
+        ctx.set_options(leaves_resident=False)
+        ctx.autotune("fp64", True, reps=1)
+        ctx.set_tile("fp64", 0, 32, -1)
+    ctx.close()
+    assert np.array_equal(got[0], got[1])

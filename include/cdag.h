@@ -424,9 +424,9 @@ int cdag_memsim(cdag_ctx* c, const int64_t* order, int64_t n, int elem_bytes,
  * without evictions is executed by its data and memory dependencies:
  * contractions of different plan steps share a launch where neither needs the
  * other's output or memory (the statistics are the plan's).  Without a budget
- * its placement may take up to 128 MiB per pass to make room for that
- * (arena_bytes says so; an arena that only holds the tightest placement is
- * taken as well). */
+ * its tensor pool may be placed wider than it has to, by at most 128 MiB per
+ * pass, to make room for that (arena_bytes and tensor_highwater say so; an
+ * arena that only holds the tightest placement is taken as well). */
 int cdag_plan(cdag_ctx* c, int prec, int batched, cdag_plan_stats* out);
 
 /* The last plan's op list: op[i] in cdag_plan_op, node[i], step[i]. */

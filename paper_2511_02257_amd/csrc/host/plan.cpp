@@ -286,9 +286,10 @@ class Pool {
 }  // namespace
 
 namespace {
-// Memory that placement may take beyond the tightest pool to keep contractions
-// of different plan steps from waiting for one another's memory: half of the
-// 256 MB last-level cache, so that intermediates still meet there.
+// Pool up to which placement takes fresh memory to keep contractions of
+// different plan steps from waiting for one another's, and the most that it
+// takes beyond the tightest pool: half of the 256 MB last-level cache, so that
+// intermediates still meet there.
 constexpr int64_t kSpreadBytes = 128LL << 20;
 // Uploads of one execution step in overlapping issue: at least this, and a
 // quarter of what the plan step uploads.
@@ -562,7 +563,9 @@ void place(const Dag& d, Plan& p) {
     Plan::Program merged = place_pool(d, p, base, 0, MERGED, &staged);
     if (p.opts.spread && p.opts.budget == INT64_MAX && p.pool_bytes < kSpreadBytes && merged.n() > 1) {
       Plan::Program wider = place_pool(d, p, base, kSpreadBytes, MERGED);
-      if (wider.n() < std::min(merged.n(), p.first.n())) merged = std::move(wider);
+      // (past the cap, where it leaves no block large enough, it may still grow)
+      const bool within = p.pool_bytes <= p.tight_pool_bytes + kSpreadBytes;
+      if (within && wider.n() < std::min(merged.n(), p.first.n())) merged = std::move(wider);
       else place_pool(d, p, base, 0, PLAN_STEPS);   // back to the tightest placement
     }
     if (merged.n() < p.first.n()) {

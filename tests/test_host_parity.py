@@ -666,3 +666,30 @@ def test_plan_keeps_to_the_static_scratch_where_only_its_tightest_placement_fits
         c.close()
     assert need[48][0] > need[48][1] and need[48][0] + need[48][2] <= B.STATIC_SCRATCH_BYTES
     assert need[64][0] == need[64][1] <= B.STATIC_SCRATCH_BYTES // 4
+
+
+@pytest.mark.parametrize("nvecs,nt,n_bar,graphs,chunks,seed", [((32, 96), 32, 3, 60, 2, 5), ((24, 48, 96), 16, 3, 60, 4, 2),
+                                                               ((16, 24, 32, 96), 8, 4, 60, 1, 1)])
+def test_wider_placement_stays_within_its_limit(nvecs, nt, n_bar, graphs, chunks, seed):
+    """Without a budget a pass's tensor pool is placed at most 128 MiB wider than
+    under a budget that does not bind, tensors of mixed sizes included (where it
+    grows past the 128 MiB up to which it takes fresh memory)."""
+    wl = W.batched_mix(nvecs=nvecs, nt=nt, n_mes=6, n_bar=n_bar, n_graphs=graphs, seed=seed, with_data=False)
+    c = X.Context()
+    c.build_cdag(wl.leaves, wl.graphs)
+    c.set_time_chunks(chunks)
+    halves, grown = 2 if chunks > 1 else 1, 0
+    for policy in ("tree", "input"):
+        c.schedule(policy)
+        for look in (0, 16, B.LOOKAHEAD_ALL):
+            for prec, eb in (("fp64", 16), ("fp32", 8)):
+                c.set_options(leaves_resident=True, wave_lookahead=look)
+                leaves = sum((eb * lf.nt * lf.nvec ** lf.rank + 255) // 256 * 256 for lf in wl.leaves)
+                c.set_mem_budget(None)
+                free = c.plan(prec, True)["tensor_highwater"] - leaves
+                c.set_mem_budget(1 << 50)
+                tight = c.plan(prec, True)["tensor_highwater"] - leaves
+                assert tight <= free <= tight + halves * (128 << 20)
+                grown += free > halves * (128 << 20) and free > tight
+    c.close()
+    assert grown > 0

@@ -208,79 +208,91 @@ int64_t align_up(int64_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // Best-fit allocator over [0, inf) that remembers, per free range, the last
 // compute step that touched the memory and the last transfer that read it
-// (device ranges: a spill; host ranges: an upload).
+// (device ranges: a spill; host ranges: an upload).  Below `cap` bytes it takes
+// fresh memory first, and then the large enough block whose last use is oldest
+// (of equally old ones the smallest).
 class Pool {
  public:
+  explicit Pool(int64_t cap = 0) : cap_(cap) {}
   struct Free { int64_t size, comp, copy; };
   int64_t top = 0;
-  std::map<int64_t, Free> free_;             // offset -> block
-  std::set<std::pair<int64_t, int64_t>> by_size;  // (size, offset)
 
   // Returns offset; *comp / *copy receive the waits inherited from the block.
-  // Best fit; while the pool is below `cap`, fresh memory first, and then the
-  // large enough block whose last use is oldest.
-  int64_t alloc(int64_t bytes, int64_t* comp, int64_t* copy, int64_t cap = 0) {
+  int64_t alloc(int64_t bytes, int64_t* comp, int64_t* copy) {
     bytes = align_up(std::max<int64_t>(bytes, 1));
-    auto it = by_size.lower_bound({bytes, -1});
-    if (cap > 0 && top + bytes <= cap) {
-      it = by_size.end();
-    } else if (cap > 0) {
-      for (auto k = it; k != by_size.end(); ++k)
-        if (free_[k->second].comp < free_[it->second].comp) it = k;
+    const bool fresh = cap_ > 0 && top + bytes <= cap_;
+    int64_t off = -1;
+    if (cap_ == 0) {
+      const auto it = by_size_.lower_bound({bytes, -1});
+      if (it != by_size_.end()) off = it->second;
+    } else if (!fresh && !by_size_.empty() && by_size_.rbegin()->first >= bytes) {
+      auto it = by_age_.begin();
+      while (std::get<1>(*it) < bytes) ++it;
+      off = std::get<2>(*it);
     }
-    if (it != by_size.end()) {
-      int64_t off = it->second;
-      Free f = free_[off];
-      by_size.erase(it);
-      free_.erase(off);
+    if (off >= 0) {
+      const Free f = take(off);
       if (f.size > bytes) put(off + bytes, {f.size - bytes, f.comp, f.copy});
       *comp = f.comp;
       *copy = f.copy;
       return off;
     }
     // extend from a free block that ends at the top, else from fresh memory
-    if (!free_.empty() && !(cap > 0 && top + bytes <= cap)) {
-      auto last = std::prev(free_.end());
+    if (!free_.empty() && !fresh) {
+      const auto last = std::prev(free_.end());
       if (last->first + last->second.size == top) {
-        int64_t off = last->first;
-        Free f = last->second;
-        by_size.erase({f.size, off});
-        free_.erase(last);
+        off = last->first;
+        const Free f = take(off);
         top = off + bytes;
         *comp = f.comp;
         *copy = f.copy;
         return off;
       }
     }
-    int64_t off = top;
+    off = top;
     top += bytes;
     *comp = -1;
     *copy = -1;
     return off;
   }
   void release(int64_t off, int64_t bytes, int64_t comp, int64_t copy) {
-    put(off, {align_up(std::max<int64_t>(bytes, 1)), comp, copy});
+    Free f{align_up(std::max<int64_t>(bytes, 1)), comp, copy};
+    const auto nx = free_.lower_bound(off);
+    if (nx != free_.end() && off + f.size == nx->first) join(&f, take(nx->first));   // merge right
+    const auto at = free_.lower_bound(off);
+    if (at != free_.begin()) {                                                      // merge left
+      const auto pv = std::prev(at);
+      if (pv->first + pv->second.size == off) {
+        off = pv->first;
+        join(&f, take(off));
+      }
+    }
+    put(off, f);
   }
 
  private:
-  void put(int64_t off, Free f) {
-    auto nx = free_.lower_bound(off);
-    if (nx != free_.end() && off + f.size == nx->first) {   // merge right
-      f = {f.size + nx->second.size, std::max(f.comp, nx->second.comp), std::max(f.copy, nx->second.copy)};
-      by_size.erase({nx->second.size, nx->first});
-      nx = free_.erase(nx);
-    }
-    if (nx != free_.begin()) {                               // merge left
-      auto pv = std::prev(nx);
-      if (pv->first + pv->second.size == off) {
-        off = pv->first;
-        f = {f.size + pv->second.size, std::max(f.comp, pv->second.comp), std::max(f.copy, pv->second.copy)};
-        by_size.erase({pv->second.size, pv->first});
-        free_.erase(pv);
-      }
-    }
+  int64_t cap_;
+  std::map<int64_t, Free> free_;                             // offset -> block
+  std::set<std::pair<int64_t, int64_t>> by_size_;            // (size, offset)
+  std::set<std::tuple<int64_t, int64_t, int64_t>> by_age_;   // (comp, size, offset); with a cap only
+
+  void put(int64_t off, const Free& f) {
     free_[off] = f;
-    by_size.insert({f.size, off});
+    by_size_.insert({f.size, off});
+    if (cap_ > 0) by_age_.insert({f.comp, f.size, off});
+  }
+  Free take(int64_t off) {
+    const auto it = free_.find(off);
+    const Free f = it->second;
+    free_.erase(it);
+    by_size_.erase({f.size, off});
+    if (cap_ > 0) by_age_.erase({f.comp, f.size, off});
+    return f;
+  }
+  static void join(Free* f, const Free& o) {
+    f->size += o.size;
+    f->comp = std::max(f->comp, o.comp);
+    f->copy = std::max(f->copy, o.copy);
   }
 };
 }  // namespace
@@ -312,7 +324,7 @@ enum Cut { PLAN_STEPS, STAGED, MERGED };
 Plan::Program place_pool(const Dag& d, Plan& p, int64_t base, int64_t cap, Cut cut, bool* staged = nullptr) {
   const int64_t n = d.n_nodes();
   const bool merge = cut != PLAN_STEPS;
-  Pool dev, host;
+  Pool dev(cap), host;
   // last_touch: execution step of the last kernels that read or wrote the
   // tensor; spilled: that of the spill that wrote its host copy; uploaded: that
   // of the last upload that read that host copy; avail: first one whose kernels
@@ -381,7 +393,7 @@ Plan::Program place_pool(const Dag& d, Plan& p, int64_t base, int64_t cap, Cut c
         break;
       case OP_H2D: {
         int64_t comp, spill;
-        off[x] = base + dev.alloc(sz, &comp, &spill, cap);
+        off[x] = base + dev.alloc(sz, &comp, &spill);
         r.dev_off = off[x];
         r.wait_comp = comp;          // kernels that last touched this memory
         if (d.is_leaf(x)) {
@@ -407,7 +419,7 @@ Plan::Program place_pool(const Dag& d, Plan& p, int64_t base, int64_t cap, Cut c
       }
       case OP_ALLOC: {
         int64_t comp, spill;
-        off[x] = base + dev.alloc(sz, &comp, &spill, cap);
+        off[x] = base + dev.alloc(sz, &comp, &spill);
         r.dev_off = off[x];
         r.wait_d2h = spill;          // a spill that last read this memory
         out_after[x] = comp + 1;     // kernels that last touched this memory

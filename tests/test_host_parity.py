@@ -693,3 +693,22 @@ def test_wider_placement_stays_within_its_limit(nvecs, nt, n_bar, graphs, chunks
                 grown += free > halves * (128 << 20) and free > tight
     c.close()
     assert grown > 0
+
+
+def test_wider_placement_does_not_dominate_planning():
+    """Planning 53,797 contractions without a budget, which looks for the free block
+    of oldest use at every allocation past 128 MiB, stays within a small
+    multiple of planning them under a budget that does not bind (the least of
+    three each; a scan of the free blocks made it 9 times as long)."""
+    wl = W.meson_ring(n_leaves=24, nvec=16, nt=4, n_graphs=20000, lmin=4, lmax=8, seed=3, with_data=False)
+    c = X.Context()
+    c.build_cdag(wl.leaves, wl.graphs)
+    c.schedule("tree")
+    c.set_options(leaves_resident=True)
+    t = {}
+    for budget in (None, 1 << 50) * 3:
+        c.set_mem_budget(budget)
+        s = c.plan("fp64", True)["t_plan_s"]
+        t[budget] = min(s, t.get(budget, s))
+    c.close()
+    assert t[None] <= 5 * t[1 << 50], t

@@ -330,7 +330,20 @@ Plan::Program place_pool(const Dag& d, Plan& p, int64_t base, int64_t cap, Cut c
   // of the last upload that read that host copy; avail: first one whose kernels
   // may read it; out_after: first one whose kernels may write it
   std::vector<int64_t> off(n, -1), hoff(n, -1), last_touch(n, -1), spilled(n, -1), uploaded(n, -1);
-  std::vector<int64_t> avail(n, 0), out_after(n, 0), in_step;
+  std::vector<int64_t> avail(n, 0), out_after(n, 0);
+  // contractions in each execution step; room[k]: k while it has room for
+  // another (wave_max), else a step on the way to the next that has
+  std::vector<int64_t> in_step, room;
+  auto with_room = [&](int64_t at) {
+    for (;; at = room[at]) {
+      for (int64_t k = (int64_t)room.size(); k <= at + 1; ++k) {
+        in_step.push_back(0);
+        room.push_back(k);
+      }
+      if (room[at] == at) return at;
+      room[at] = room[room[at]];
+    }
+  };
   if (p.opts.leaves_resident)
     for (int64_t u = 0; u < d.n_leaves; ++u) off[u] = p.leaf_off[u];
   // A step with more uploads than one stage stages its smaller tensors first (a
@@ -431,11 +444,8 @@ Plan::Program place_pool(const Dag& d, Plan& p, int64_t base, int64_t cap, Cut c
         r.b_off = off[b];
         r.dev_off = d.kind[x] == HCA ? -1 : off[x];
         if (merge) {
-          int64_t at = std::max({avail[a], avail[b], out_after[x], floor_x});
-          if ((int64_t)in_step.size() <= at) in_step.resize(at + 1, 0);
-          while (in_step[at] >= p.opts.wave_max)
-            if (++at == (int64_t)in_step.size()) in_step.push_back(0);
-          ++in_step[at];
+          const int64_t at = with_room(std::max({avail[a], avail[b], out_after[x], floor_x}));
+          if (++in_step[at] >= p.opts.wave_max) room[at] = at + 1;
           r.xstep = at;
           avail[x] = at + 1;
         }

@@ -712,3 +712,26 @@ def test_wider_placement_does_not_dominate_planning():
         t[budget] = min(s, t.get(budget, s))
     c.close()
     assert t[None] <= 5 * t[1 << 50], t
+
+
+def test_small_waves_do_not_dominate_planning():
+    """Waves of one contraction are planned in a small multiple of the time that
+    full waves take (the next execution step with room is looked up, not
+    counted up to: 103,216 contractions of which 63,216 are ready at once took
+    26 times as long)."""
+    rng = np.random.default_rng(4)
+    leaves = [W.Leaf(2, 4, 1) for _ in range(400)]
+    graphs = []
+    for _ in range(20000):
+        a, b, c, d = (int(x) for x in rng.choice(400, 4, replace=False))
+        graphs.append(W.GraphSpec([(W.K22, a, b), (W.K22, c, d), (W.HCA, -1, -2)]))
+    ctx = X.Context()
+    ctx.build_cdag(leaves, graphs)
+    ctx.schedule("input")
+    t = {}
+    for wave_max in (1, 4096) * 3:
+        ctx.set_options(leaves_resident=True, wave_max=wave_max)
+        s = ctx.plan("fp64", True)["t_plan_s"]
+        t[wave_max] = min(s, t.get(wave_max, s))
+    ctx.close()
+    assert t[1] <= 5 * t[4096], t

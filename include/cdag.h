@@ -323,13 +323,14 @@ int set_mem_budget(cdag_ctx* c, uint64_t bytes);
  * wave in batched mode (default 4096).  wave_lookahead: in batched mode a wave
  * takes the ready contractions (operands are leaves or earlier waves' outputs)
  * in schedule order and may pass over this many not-ready ones (default 0:
- * the schedule order is kept exactly; INT64_MAX: every ready contraction).
+ * the waves keep the schedule order exactly; INT64_MAX: every ready
+ * contraction; cdag_plan says which waves are then executed together).
  * use_graphs: 0 issues every step eagerly on three streams (kernels, uploads,
  * spills) with event waits from the plan; 1 (default) replays captured HIP
  * graphs with every step on one stream (one graph, or segments of 64 steps
- * when the plan moves data); 2 replays one captured graph over the three
- * streams with the plan's waits as graph edges (uploads and spills overlap
- * kernels).  CDAG_E_INVALID for wave_max < 1, a negative lookahead or another
+ * when the plan moves data); 2 replays one graph in which a step's transfers
+ * of up to 8 MiB are in sequence with the kernels and larger ones beside them,
+ * with the plan's waits as edges.  CDAG_E_INVALID for wave_max < 1, a negative lookahead or another
  * use_graphs. */
 int cdag_set_options(cdag_ctx* c, int leaves_resident, int wave_max, int64_t wave_lookahead,
                      int use_graphs);
@@ -364,7 +365,9 @@ int cdag_set_trace_fusion(cdag_ctx* c, int on);
 /* timing: 1 records a HIP event pair around every kernel launch on the
  * compute stream and around every host transfer on its stream, reports
  * the summed exterior-contraction durations in t_hec_s and keeps per-launch
- * and per-transfer records (execution then runs without graph replay);
+ * and per-transfer records (execution then runs without graph replay, and
+ * every transfer is a copy of its own, so that it has a duration; otherwise
+ * the transfers of a step and direction are one launch up to 8 MiB);
  * 0 (default) turns it off. */
 int cdag_set_timing(cdag_ctx* c, int timing);
 /* Host-only: the eager three-stream issue order that execute would follow for
@@ -403,9 +406,12 @@ int cdag_launch_records(cdag_ctx* c, cdag_launch_record* out, int64_t cap, int64
  * work item per output tile, the whole K in one accumulator).
  * Without an explicit choice a default by N applies (split_k 1;
  * cdag_get_tile reports it): its product form and its K splits, on the tile of
- * that form that suits the contraction's GEMM, with one LDS stage (launch
- * records report the variant that ran; variant 30 is a 128x128 tile of 512
- * threads, split BF16 only).  Every choice gives results
+ * that form that suits the contraction's GEMM, with one LDS stage; setting the
+ * reported choice runs that very tile instead, with two stages and mostly
+ * slower.  Launch records report the variant that ran: tile + 6 * (grid + 2 *
+ * (2 - lds_stages)) for a choice, 24 for contractions over any index pairs,
+ * and, where no choice was made only, 30 (128x128, 512 threads, split BF16)
+ * and 36 (64x80, 256 threads, FP64 and FP32).  Every choice gives results
  * within the precision's bound; bits may differ between choices, never with
  * the grouping of contractions into launches. */
 int cdag_set_tile(cdag_ctx* c, int prec, int kind, int nvec, int tile, int grid, int lds_stages,

@@ -276,7 +276,7 @@ GRAPH_MODES = {0: "eager", 1: "one-stream segments", 2: "three-stream graph"}
 def cdag_set_options(h, leaves_resident=False, wave_max=4096, wave_lookahead=0,
                      use_graphs=1) -> None:
     """use_graphs: 0 (or False) eager, 1 (or True) one-stream captured segments,
-    2 one three-stream captured graph."""
+    2 one graph with large transfers beside the kernels."""
     _check(lib().cdag_set_options(h, int(leaves_resident), int(wave_max), int(wave_lookahead),
                                   int(use_graphs)))
 
@@ -446,11 +446,14 @@ def _rows(fetch, h, nts: Sequence[int]) -> List[np.ndarray]:
 
 
 def fetch_correlators(h, nts: Sequence[int]) -> List[np.ndarray]:
-    """Per input graph, complex128 [nt(g)]; nts: Nt of each graph in input order."""
+    """Per input graph, complex128 [nt(g)]; nts: Nt of each graph in input order.
+    The rows are views of one array of this call; copy a row to keep it without
+    the others."""
     return _rows(lib().fetch_correlators, h, nts)
 
 
 def cdag_fetch_sums(h, nts: Sequence[int]) -> List[np.ndarray]:
+    """Per correlator, complex128 [nt(c)], views like fetch_correlators'."""
     return _rows(lib().cdag_fetch_sums, h, nts)
 
 

@@ -311,9 +311,13 @@ constexpr int64_t kStageBytes = 32LL << 20;
 constexpr int64_t kFewSteps = 32;
 constexpr double kLongStep = 100e-6;
 
-// modelled_time(): launch and latency of a step, compute units, and the share of
-// the plan steps' time that another cut has to stay below.
-constexpr double kStepTime = 7e-6, kUnits = 256, kWorthCutting = 0.99;
+// modelled_time(): launch and latency of a step, compute units.
+constexpr double kStepTime = 7e-6, kUnits = 256;
+// Shares of a modelled time that another cut has to stay below to be taken in its
+// place: any cut for the plan steps' (or, where contractions fill kFilled of it,
+// so that a cut costs little), plan steps for STAGED in the later passes, MERGED
+// for either (see place()).
+constexpr double kWorthCutting = 0.99, kFilled = 0.95, kBelowFilled = 0.998, kBelowStaged = 0.998, kBelowUncut = 0.98;
 
 // How execution steps are cut (place()).
 enum Cut { PLAN_STEPS, STAGED, MERGED };
@@ -545,17 +549,23 @@ double modelled_time(const Dag& d, const Plan& p, const Plan::Program& first, co
 // steps, so it has to hide more of the uploads than they cost: a step takes at
 // least as long as its longest work item (a K33 item with the whole K: 0.5 ms).
 // The passes are modelled (modelled_time()), the first MERGED, which also moves
-// later plan steps' contractions up between the stages, and the later ones as
-// the plan's steps, STAGED or MERGED; the plan's steps stay unless a cut is
-// modelled at least 1 % shorter.  Measured (ms; baryon chains at N = 64, 8
-// passes, FP64, K33 in whole items; by plan steps, then with the later passes
-// as planned, STAGED, MERGED; * what the model takes):
-//   every ready contraction in a wave, 24 plan steps   38.0  36.7  36.0*  44.1
-//   lookahead 64, 184                                  82.6* 82.7  86.1   92.5
-//   Sibling, lookahead 16, 576                        253.6* 253.8 266.3 266.6
-// and five N families in 4 passes, FP32, lookahead 64   35.0  33.1  31.5  30.2*
-// (with the model in FP64 in place of a rule on the pass's upload and
-// contraction times alone: 67.8 -> 62.4).
+// later plan steps' contractions up between the stages, and the later ones
+// STAGED, as the plan's steps or MERGED; the plan's steps stay unless a cut is
+// modelled at least 1 % shorter (node order, the third line below: modelled 0.6 %
+// shorter, measured 1.5 % longer), or 0.2 % where contractions fill the time
+// (20,301 contractions in 16 passes: modelled 0.7 % shorter, 832 -> 818 ms).
+// Where cuts are modelled alike the smaller launches of STAGED come out ahead by
+// up to 1 % (the same in 8 passes 787 against 793 ms with the model 0.02 % the
+// other way), and MERGED behind by up to 6 % (40.4 against 38.0, modelled 0.5 %
+// the other way): hence the margins.  Measured (ms; baryon chains at N = 64, 8 passes, FP64, K33 in
+// whole items; by plan steps, then with the later passes as planned, STAGED,
+// MERGED; * what is taken):
+//   every ready contraction in a wave, 24 plan steps   38.0   36.7  36.0*  44.1
+//   lookahead 64, 184                                  82.6*  82.7  86.1   92.5
+//   node order, lookahead 16, 552                     258.8* 259.6 264.7  262.8
+//   Sibling, lookahead 16, 576                        253.6* 253.8 266.3  266.6
+// and five N families in 4 passes, lookahead 64: FP32   35.0   33.1  31.5   30.2*
+//                                                FP64   65.2   66.0  62.4*  67.8
 // Plans of many long steps keep their plan steps: launches cost them nothing,
 // and a contraction that moves up leaves its output waiting for its consumer
 // long enough to drop out of the last-level cache (20,301 contractions in 1,151
@@ -595,13 +605,15 @@ void place(const Dag& d, Plan& p) {
     } else if (staged) {
       const Plan::Program cut = place_pool(d, p, base, 0, STAGED);
       const Plan::Program* later = nullptr;
-      double best = modelled_time(d, p, p.first, p.first) * kWorthCutting;
-      const Plan::Program* const cuts[] = {&p.first, &cut, &merged};
-      for (const Plan::Program* l : cuts) {
-        const double t = modelled_time(d, p, merged, *l);
-        if (t < best) {
+      const double t_plan = modelled_time(d, p, p.first, p.first);
+      double best = t_plan * (t_pass * (double)p.chunks() > kFilled * t_plan ? kBelowFilled : kWorthCutting);
+      const struct { const Plan::Program* cut; double below; } later_cuts[] = {
+          {&cut, 1.0}, {&p.first, kBelowStaged}, {&merged, kBelowUncut}};
+      for (const auto& l : later_cuts) {
+        const double t = modelled_time(d, p, merged, *l.cut);
+        if (t < best * (later != nullptr ? l.below : 1.0)) {
           best = t;
-          later = l;
+          later = l.cut;
         }
       }
       if (later != nullptr) {

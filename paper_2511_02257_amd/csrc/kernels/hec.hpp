@@ -237,9 +237,6 @@ template <> struct Mfma<float> {
   static __device__ __forceinline__ int row(int grp, int v) { return 4 * grp + v; }
 };
 
-template <typename T> struct Vec2;
-template <> struct Vec2<double> { typedef double2 V; static constexpr int n = 2; };
-template <> struct Vec2<float> { typedef float4 V; static constexpr int n = 4; };
 // 16 bytes of T as one register tuple.  Loaded operands are kept in these, so
 // that every 16-byte load fills a whole tuple that stays live until its LDS
 // store (a load into a tuple the compiler only partly keeps makes it wait for

@@ -717,8 +717,8 @@ def test_wider_placement_does_not_dominate_planning():
 def test_small_waves_do_not_dominate_planning():
     """Waves of one contraction are planned in a small multiple of the time that
     full waves take (the next execution step with room is looked up, not
-    counted up to: 103,216 contractions of which 63,216 are ready at once took
-    26 times as long)."""
+    counted up to: 20,000 graphs of two contractions and a trace each took 16 times
+    as long)."""
     rng = np.random.default_rng(4)
     leaves = [W.Leaf(2, 4, 1) for _ in range(400)]
     graphs = []

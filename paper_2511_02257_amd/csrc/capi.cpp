@@ -78,7 +78,7 @@ void ensure_plan(Ctx& c, int prec, int batched, uint64_t arena) {
   constexpr double kFlopRate[4] = {65e12, 110e12, 200e12, 140e12};
   o.flop_rate = kFlopRate[prec];
   c.plan = make_plan(c.dag, c.order, o);
-  c.plan.opts.item_flops = item_flops(c.dag, prec, c.tiles);
+  if (o.overlap && o.batched) c.plan.opts.item_flops = item_flops(c.dag, prec, c.tiles);
   place(c.dag, c.plan);
   c.kplan = make_kernel_plan(c.dag, c.plan, prec, c.tiles, c.fuse_traces);
   // the tightest placement where only that fits the arena, or the static scratch

@@ -557,9 +557,9 @@ double modelled_time(const Dag& d, const Plan& p, const Plan::Program& first, co
 // Where cuts are modelled alike the smaller launches of STAGED come out ahead by
 // up to 1 % (the same in 8 passes 787 against 793 ms with the model 0.02 % the
 // other way), and MERGED behind by up to 6 % (40.4 against 38.0, modelled 0.5 %
-// the other way): hence the margins.  Measured (ms; baryon chains at N = 64, 8 passes, FP64, K33 in
-// whole items; by plan steps, then with the later passes as planned, STAGED,
-// MERGED; * what is taken):
+// the other way): hence the margins.  Measured (ms; baryon chains at N = 64, 8
+// passes, FP64, K33 in whole items; by plan steps, then with the later passes as
+// planned, STAGED, MERGED; * what is taken):
 //   every ready contraction in a wave, 24 plan steps   38.0   36.7  36.0*  44.1
 //   lookahead 64, 184                                  82.6*  82.7  86.1   92.5
 //   node order, lookahead 16, 552                     258.8* 259.6 264.7  262.8

@@ -997,3 +997,26 @@ def test_synthetic_autotune_between_resident_executes():
         ctx.set_tile("fp64", 0, 32, -1)
     ctx.close()
     assert np.array_equal(got[0], got[1])
+
+
+def test_graph_with_large_transfers_in_many_passes():
+    """Issue mode 2 over 8 passes whose uploads are copy nodes beside the kernels
+    (over 8 MiB a step; the mesons' smaller ones in the chain): every replay
+    gives the bits of resident leaves."""
+    import paper_2511_02257_amd as X
+    from paper_2511_02257_amd.device import DeviceRunner
+    wl = W.baryon_mix(n_bar=4, n_mes=4, nvec=64, nt=8, n_graphs=12, sigma=1 / 64, n_corr=2, seed=82)
+    ctx = X.Context()
+    ctx.build_cdag(wl.leaves, wl.graphs)
+    ctx.schedule("tree")
+    runner = DeviceRunner(ctx, 0)
+    ctx.set_options(leaves_resident=True)
+    runner.run("fp64", True)
+    want = np.concatenate(ctx.fetch_correlators()).view(np.uint64).copy()
+    ctx.set_time_chunks(8)
+    for look in (0, (1 << 63) - 1):
+        ctx.set_options(leaves_resident=False, wave_lookahead=look, use_graphs=2)
+        for _ in range(3):
+            runner.run("fp64", True)
+            assert np.array_equal(np.concatenate(ctx.fetch_correlators()).view(np.uint64), want), look
+    ctx.close()
